@@ -44,7 +44,7 @@ __device__ inline void adj_surface_of(const Geo& G, const DevBasis& sb, const do
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
   const int nS = G.nSides;
   for (int ft = t; ft < S::nface; ft += S::nth) {
-    const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
+    const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
     const int info = G.efc[e * 6 + f];
     const int side = efc_side(info), slot = efc_slot(info);
     int p = pp, q = qq;
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
   double fno[3] = {0, 0, 0};
   size_t fqi = 0;
   for (int ft = t; ft < S::nface; ft += S::nth) {
-    const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1;
+    const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1;
     const int info = G.efc[e * 6 + f];
     const int side = efc_side(info), slot = efc_slot(info);
     int p = pp, qm = qq;
@@ -213,9 +213,9 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
         gR[c] = gtr[tr_index(1, c, 12, nS, side, n2, fi)];
       }
     }
-    const double nh[3] = {G.face[((size_t)0 * nS + side) * n2 + fi], G.face[((size_t)1 * nS + side) * n2 + fi],
-                          G.face[((size_t)2 * nS + side) * n2 + fi]};
-    const double s = G.face[((size_t)3 * nS + side) * n2 + fi];
+    const FaceGeom fg = face_geom(G, info, n2, fi);
+    const double nh[3] = {fg(0), fg(1), fg(2)};
+    const double s = fg(3);
     if constexpr (kOneFaceNode && PHYS == 1) {
       const double sgn = slot ? -1.0 : 1.0;
 #pragma unroll
@@ -362,9 +362,10 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
         if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
         const int fi = qm * n1 + p;
         const double sgn = slot ? -1.0 : 1.0;
-        const double s = G.face[((size_t)3 * nS + side) * n2 + fi];
+        const FaceGeom fg = face_geom(G, info, n2, fi);
+        const double s = fg(3);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) no[c] = sgn * (G.face[((size_t)c * nS + side) * n2 + fi] * s);
+        for (int c = 0; c < 3; ++c) no[c] = sgn * (fg(c) * s);
         qi = tr_index(slot, 0, 4, nS, side, n2, fi);
       }
       double acc[4] = {0, 0, 0, 0};

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -662,16 +663,38 @@ dg_status dg_set_mesh(dg_ctx* c, int nElems, int Ngeo, const double* X, int nSid
   return DG_OK;
 }
 
+// The normals and surface elements (Geo::face): per face node, and once per
+// side for the sides whose nodes bitwise share them (unless per-element metric
+// terms are switched off); those sides are marked in the device's face table.
 static dg_status upload_face(dg_ctx* c, const std::vector<double>& nvec) {
-  const size_t nf = (size_t)c->nSides * c->n2;
-  std::vector<double> face(4 * nf);
-  for (size_t t = 0; t < nf; ++t) {
-    double a = nvec[t], b = nvec[nf + t], d = nvec[2 * nf + t];
-    double s = std::sqrt(a * a + b * b + d * d);
-    if (!(s > 0.0)) return fail(c, DG_ERR_MESH, "zero face normal");
-    face[t] = a / s; face[nf + t] = b / s; face[2 * nf + t] = d / s; face[3 * nf + t] = s;
-  }
+  const size_t nS = c->nSides, n2 = c->n2, nf = nS * n2;
+  std::vector<double> face(4 * nf + 4 * nS, 0.0);
+  std::vector<char> same(nS, 0);
+  std::atomic<bool> zero{false};
+  auto side_block = [&](size_t s0, size_t s1) {
+    for (size_t s = s0; s < s1; ++s) {
+      bool eq = c->elem_metrics;
+      for (size_t t = s * n2; t < (s + 1) * n2; ++t) {
+        double a = nvec[t], b = nvec[nf + t], d = nvec[2 * nf + t];
+        double sf = std::sqrt(a * a + b * b + d * d);
+        if (!(sf > 0.0)) { zero = true; return; }
+        face[t] = a / sf; face[nf + t] = b / sf; face[2 * nf + t] = d / sf; face[3 * nf + t] = sf;
+        for (int k = 0; k < 4; ++k) eq = eq && face[k * nf + t] == face[k * nf + s * n2];
+      }
+      same[s] = eq;
+      for (int k = 0; k < 4; ++k) face[4 * nf + k * nS + s] = face[k * nf + s * n2];
+    }
+  };
+  const int nth = host_threads(c->nSides, 256);
+  std::vector<std::thread> pool;
+  for (int th = 0; th < nth; ++th) pool.emplace_back(side_block, nS * th / nth, nS * (th + 1) / nth);
+  for (auto& th : pool) th.join();
+  if (zero) return fail(c, DG_ERR_MESH, "zero face normal");
+  std::vector<int> efc(c->efc);
+  for (int& v : efc)
+    if (same[efc_side(v)]) v |= kEfcConst;
   HIPCHK(c, hipMemcpy(c->d_face, face.data(), face.size() * sizeof(double), hipMemcpyHostToDevice));
+  HIPCHK(c, hipMemcpy(c->d_efc, efc.data(), efc.size() * sizeof(int), hipMemcpyHostToDevice));
   return DG_OK;
 }
 
@@ -741,7 +764,7 @@ dg_status dg_upload_mesh(dg_ctx* c, int nElems, int Ngeo, const double* X, int n
   const size_t nv = (size_t)c->nElems * c->n3, nf = (size_t)c->nSides * c->n2;
   hipError_t e;
   if ((e = hipMalloc((void**)&c->d_Ja, 10 * nv * sizeof(double))) != hipSuccess ||
-      (e = hipMalloc((void**)&c->d_face, 4 * nf * sizeof(double))) != hipSuccess ||
+      (e = hipMalloc((void**)&c->d_face, 4 * (nf + c->nSides) * sizeof(double))) != hipSuccess ||
       (e = hipMalloc((void**)&c->d_efc, (size_t)c->nElems * 6 * sizeof(int))) != hipSuccess ||
       (e = hipMalloc((void**)&c->d_basis, sizeof(DevBasis))) != hipSuccess) {
     free_device(c);
@@ -751,7 +774,6 @@ dg_status dg_upload_mesh(dg_ctx* c, int nElems, int Ngeo, const double* X, int n
   c->d_sJ = c->d_Ja + 9 * nv;
   HIPCHK(c, hipMemcpy(c->d_Ja, c->Ja.data(), 9 * nv * sizeof(double), hipMemcpyHostToDevice));
   HIPCHK(c, hipMemcpy(c->d_sJ, c->sJ.data(), nv * sizeof(double), hipMemcpyHostToDevice));
-  HIPCHK(c, hipMemcpy(c->d_efc, c->efc.data(), (size_t)c->nElems * 6 * sizeof(int), hipMemcpyHostToDevice));
   HIPCHK(c, hipMemcpy(c->d_basis, &c->hb, sizeof(DevBasis), hipMemcpyHostToDevice));
   st = upload_face(c, c->nvec);
   if (st != DG_OK) return st;
@@ -831,7 +853,9 @@ dg_status dg_get_metrics(const dg_ctx* cc, double* xyz, double* Ja, double* sJ, 
 dg_status dg_set_element_metrics(dg_ctx* c, int enable) {
   if (!c) return fail(nullptr, DG_ERR_ARG, "dg_set_element_metrics: null context");
   c->elem_metrics = enable != 0;
-  return c->mesh_on_device ? upload_elem_metrics(c) : DG_OK;
+  if (!c->mesh_on_device) return DG_OK;
+  dg_status st = upload_face(c, c->nvec);
+  return st == DG_OK ? upload_elem_metrics(c) : st;
 }
 
 dg_status dg_element_metric_count(const dg_ctx* c, int* count) {

@@ -27,9 +27,13 @@ struct DevBasis {
   double Vli[kMaxN1 * kMaxN1];    // inverse of the orthonormal-Legendre Vandermonde V[i*n1+m] = P~_m(x_i)
 };
 
-// Per-element face table entry: side index, slot (0 master / 1 slave), orientation.
+// Per-element face table entry: side index (27 bits), slot (0 master /
+// 1 slave), orientation; in the device copy the sign bit marks sides whose
+// normal and surface element are the same at all of their nodes (Geo::face).
 __host__ __device__ inline int efc_pack(int side, int slot, int orient) { return (side << 4) | (slot << 3) | orient; }
-__host__ __device__ inline int efc_side(int v) { return v >> 4; }
+__host__ __device__ inline int efc_side(int v) { return (v & 0x7fffffff) >> 4; }
+__host__ __device__ inline bool efc_const(int v) { return v < 0; }
+constexpr int kEfcConst = (int)0x80000000;
 __host__ __device__ inline int efc_slot(int v) { return (v >> 3) & 1; }
 __host__ __device__ inline int efc_orient(int v) { return v & 7; }
 
@@ -65,7 +69,9 @@ struct Geo {
   // its nodes (affine elements): Ja^r_n at 3r+n, 1/J at 9; 1/J = 0 (the
   // sign test em[9][e] > 0) sends the element's kernels to Ja and sJ
   const double* em;
-  const double* face;    // [4][nSides][n2]: unit normal (3), surface element
+  // [4][nSides][n2]: unit normal (3), surface element; followed by [4][nSides],
+  // the same values once per side where all nodes of the side share them
+  const double* face;
   const int* efc;        // [nElems][6]
   const DevBasis* basis;
   // FV sub-cells (null unless enabled)

@@ -206,7 +206,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
   // other side's trace comes from memory; on LG nodes both traces are read.
   // UO holds the other side's trace (LGL) or the master's (LG), UR the slave's (LG).
   auto face_avg = [&](int ft, int slot, const double UO[5], const double UR[5], const double nsf[4]) {
-    const int f = ft / n2, rr = ft % n2;
+    const int f = face_of<N>(ft), rr = ft % n2;
     double qa[4], qb[4];
     {
       const Prim a = cons2prim(UO, P.gm1);
@@ -228,13 +228,14 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
     for (int c = 0; c < 3; ++c) sf[(f * 7 + 4 + c) * n2 + rr] = sgn * (nsf[c] * nsf[3]);
   };
   auto face_load = [&](int ft, int& slot, double UO[5], double UR[5], double nsf[4]) {
-    const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1;
+    const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1;
     const int info = G.efc[e * 6 + f];
     const int side = efc_side(info);
     slot = efc_slot(info);
     int p = pp, qm = qq;
     if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
     const int fi = qm * n1 + p;
+    const FaceGeom fg = face_geom(G, info, n2, fi);
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       if constexpr (NODES == 1) {
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
       }
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) nsf[c] = G.face[((size_t)c * nS + side) * n2 + fi];
+    for (int c = 0; c < 4; ++c) nsf[c] = fg(c);
   };
   // Every global load of this phase is issued before the first use: the
   // node's state, metrics and 1/J, and (when each face node has a work-item
@@ -336,9 +337,10 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) sfq[(f * 8 + 4 + c) * n2 + rr] = qo[c];
-      const double sgn = slot ? -1.0 : 1.0, sA = G.face[((size_t)3 * nS + side) * n2 + fi];
+      const FaceGeom fg = face_geom(G, info, n2, fi);
+      const double sgn = slot ? -1.0 : 1.0, sA = fg(3);
 #pragma unroll
-      for (int c = 0; c < 3; ++c) sf[(f * 7 + 4 + c) * n2 + rr] = sgn * (G.face[((size_t)c * nS + side) * n2 + fi] * sA);
+      for (int c = 0; c < 3; ++c) sf[(f * 7 + 4 + c) * n2 + rr] = sgn * (fg(c) * sA);
     }
     if (efl & 63) {
       __syncthreads();
@@ -479,10 +481,10 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
     }
   }
   // face-normal viscous flux of one side from its state trace qt and gradient trace gf
-  auto emit_face = [&](int slot, int side, int fi, const Prim& qt, const double gf[12]) {
-    const double nh[3] = {G.face[((size_t)0 * nS + side) * n2 + fi], G.face[((size_t)1 * nS + side) * n2 + fi],
-                          G.face[((size_t)2 * nS + side) * n2 + fi]};
-    const double s = G.face[((size_t)3 * nS + side) * n2 + fi];
+  auto emit_face = [&](int info, int slot, int side, int fi, const Prim& qt, const double gf[12]) {
+    const FaceGeom fg = face_geom(G, info, n2, fi);
+    const double nh[3] = {fg(0), fg(1), fg(2)};
+    const double s = fg(3);
     const double nv[3] = {nh[0] * s, nh[1] * s, nh[2] * s};
     double Gn[4];
     viscous_flux<FT, VL>(qt, gf, P, nv, Gn);
@@ -508,7 +510,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
 #pragma unroll
           for (int c = 0; c < 12; ++c) gtr[tr_index(slot, c, 12, nS, side, n2, qm * n1 + p)] = acc[c];
         } else {
-          emit_face(slot, side, qm * n1 + p, q, acc);   // LGL: the node's state is its trace
+          emit_face(info, slot, side, qm * n1 + p, q, acc);   // LGL: the node's state is its trace
         }
       }
     }
@@ -545,7 +547,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
         double ut[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) ut[v] = Utr[tr_index(slot, v, TNV, nS, side, n2, qm * n1 + p)];
-        emit_face(slot, side, qm * n1 + p, cons2prim(ut, P.gm1), gf);
+        emit_face(info, slot, side, qm * n1 + p, cons2prim(ut, P.gm1), gf);
       }
     }
   }
@@ -792,9 +794,9 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
       UL[v] = Utr[tr_index(0, v, TNV, nS, side, n2, fi)];
       UR[v] = Utr[tr_index(1, v, TNV, nS, side, n2, fi)];
     }
-    const double nh[3] = {G.face[((size_t)0 * nS + side) * n2 + fi], G.face[((size_t)1 * nS + side) * n2 + fi],
-                          G.face[((size_t)2 * nS + side) * n2 + fi]};
-    const double s = G.face[((size_t)3 * nS + side) * n2 + fi];
+    const FaceGeom fg = face_geom(G, info, n2, fi);
+    const double nh[3] = {fg(0), fg(1), fg(2)};
+    const double s = fg(3);
     double Phi[5];
     Aux own;
     if constexpr (ES) {
@@ -824,7 +826,10 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
   };
   // 1. surface fluxes of the six faces (other forms)
   if constexpr (!ES) {
-    for (int ft = t; ft < S::nface; ft += S::nth) face_node(ft / n2, ft % n2, ft / n2);
+    for (int ft = t; ft < S::nface; ft += S::nth) {
+      const int f = face_of<N>(ft);
+      face_node(f, ft % n2, f);
+    }
   }
   if constexpr (ES && kFvf) {
     if (efl & 63) {

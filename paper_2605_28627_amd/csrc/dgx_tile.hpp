@@ -61,6 +61,36 @@ __device__ __forceinline__ NodeMetric node_metric(const Geo& G, int e, int n3, i
   return m;
 }
 
+// Face f of face node ft.  With 64 face nodes (N = 7) a wavefront's lanes lie
+// on one face: telling the compiler so moves the face table, the side's
+// address arithmetic and constant normals to scalar registers.
+template <int N>
+__device__ __forceinline__ int face_of(int ft) {
+  constexpr int n2 = (N + 1) * (N + 1);
+  if constexpr (n2 == 64)
+    return __builtin_amdgcn_readfirstlane(ft / n2);
+  else
+    return ft / n2;
+}
+
+// Normal (c = 0..2) and surface element (c = 3) of face node fi of a side: the
+// side's own entry where its nodes share them (the faces of affine elements:
+// 32 B per side instead of 32 B per face node, 24 B per node and evaluation at
+// N = 7 and 48 B at N = 3), else the node's.  Both live in one array.
+struct FaceGeom {
+  const double* base;
+  size_t st;
+  __device__ __forceinline__ double operator()(int c) const { return base[c * st]; }
+};
+__device__ __forceinline__ FaceGeom face_geom(const Geo& G, int info, int n2, int fi) {
+  const size_t nS = G.nSides, nf = nS * n2, side = efc_side(info);
+  const bool cs = efc_const(info);
+  FaceGeom g;
+  g.base = G.face + (cs ? 4 * nf + side : side * n2 + fi);
+  g.st = cs ? nS : nf;
+  return g;
+}
+
 // Element of a one-element-per-workgroup launch.  Consecutive workgroups are
 // dealt round-robin to the chip's 8 XCDs, each with its own L2.  With
 // XCD-aware numbering (DGX_XCD_REMAP 1) XCD x walks a contiguous block of
