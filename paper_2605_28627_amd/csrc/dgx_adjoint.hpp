@@ -185,7 +185,12 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
     load_row(0); load_row(1); load_row(2);
     load_g();
   }
-  // 1. surface: adjoint of each side's flux, own trace part into LDS.  When
+  // 1. surface: adjoint of each side's flux with respect to the own state and
+  // gradient, into LDS.  On LGL nodes both are the face node's own values, read
+  // from the element's node arrays (its own loads' cache lines) and not from
+  // the traces; the other side's gradient is not needed at all.  N = 7 LGL:
+  // 246 B per node less (both sides' 12 gradient traces read and written and
+  // the own state trace).  When
   // every face node has a work-item of its own, that work-item keeps the
   // outward n s and the Qbar index of its face node for the lifting adjoint.
   constexpr bool kOneFaceNode = S::nface <= S::nth;
@@ -198,20 +203,18 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
     int p = pp, qm = qq;
     if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
     const int fi = qm * n1 + p;
-    double UL[5], UR[5], Phib[5];
+    double Uo[5], Un[5], Phib[5], go[PHYS == 1 ? 12 : 1];
+    const size_t tn = (size_t)e * n3 + line_node<N>(f / 2, (f & 1) ? N : 0, pp, qq);
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      UL[v] = Utr[tr_index(0, v, 5, nS, side, n2, fi)];
-      UR[v] = Utr[tr_index(1, v, 5, nS, side, n2, fi)];
+      Un[v] = Utr[tr_index(1 - slot, v, 5, nS, side, n2, fi)];
+      Uo[v] = NODES == 1 ? U[(size_t)v * nE * n3 + tn] : Utr[tr_index(slot, v, 5, nS, side, n2, fi)];
       Phib[v] = Lbar[tr_index(0, v, 5, nS, side, n2, fi)] - Lbar[tr_index(1, v, 5, nS, side, n2, fi)];
     }
-    double gL[12], gR[12];
     if constexpr (PHYS == 1) {
 #pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        gL[c] = gtr[tr_index(0, c, 12, nS, side, n2, fi)];
-        gR[c] = gtr[tr_index(1, c, 12, nS, side, n2, fi)];
-      }
+      for (int c = 0; c < 12; ++c)
+        go[c] = NODES == 1 ? gin[(size_t)c * nE * n3 + tn] : gtr[tr_index(slot, c, 12, nS, side, n2, fi)];
     }
     const FaceGeom fg = face_geom(G, info, n2, fi);
     const double nh[3] = {fg(0), fg(1), fg(2)};
@@ -222,18 +225,17 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
       for (int c = 0; c < 3; ++c) fno[c] = sgn * (nh[c] * s);
       fqi = tr_index(slot, 0, 4, nS, side, n2, fi);
     }
-    double ULb[5], URb[5], gLb[12], gRb[12];
-    surface_flux_vjp<FORM, PHYS, ROE, VL>(UL, UR, gL, gR, nh, s, P, Phib, ULb, URb, gLb, gRb);
-    // (element-wise selects keep both sides' adjoints in registers)
+    double Uob[5], gob[12];
+    surface_flux_vjp_own<FORM, PHYS, ROE, VL>(Uo, Un, go, slot, nh, s, P, Phib, Uob, gob);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sB[(f * NF + v) * n2 + rr] = slot ? URb[v] : ULb[v];
+    for (int v = 0; v < 5; ++v) sB[(f * NF + v) * n2 + rr] = Uob[v];
     if constexpr (ES) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) sub[(f * 5 + v) * n2 + rr] = slot ? URb[v] : ULb[v];
+      for (int v = 0; v < 5; ++v) sub[(f * 5 + v) * n2 + rr] = Uob[v];
     }
     if constexpr (PHYS == 1) {
 #pragma unroll
-      for (int c = 0; c < 12; ++c) sB[(f * NF + 5 + c) * n2 + rr] = slot ? gRb[c] : gLb[c];
+      for (int c = 0; c < 12; ++c) sB[(f * NF + 5 + c) * n2 + rr] = gob[c];
     }
   }
   __syncthreads();
@@ -453,7 +455,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
 #pragma unroll
       for (int v = 0; v < 5; ++v) lm[v] = sl[v * n3 + t];
     }
-    const double c1 = 0.5 / P.gm1;
+    const double c1 = P.c1;
     AuxBar ab{};
 #pragma unroll
     for (int r = 0; r < 3; ++r) {

@@ -147,7 +147,8 @@ __device__ inline double ld_visc(const double* p, size_t i) {
 
 // ---------------------------------------------------------------------------
 // BR1 lifting kernel (paper eq. dgsem_lifted), g = grad (u, v, w, T).
-// EMIT 0: g -> gout[12][nE][n3] and its face traces -> gtr[slot][12][side][fi].
+// EMIT 0: g -> gout[12][nE][n3] and, on Gauss nodes, its face traces ->
+// gtr[slot][12][side][fi].
 // EMIT 1: what the residual consumes instead of g, formed here:
 //   gout[v][nE][n3] = -sum_r sum_l Dhat[a_r][l] G~^r_v(l)   (v = 0..3: the
 //       viscous part of the weak-form volume term for rho u, rho v, rho w, rho e,
@@ -491,9 +492,9 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
 #pragma unroll
     for (int v = 0; v < 4; ++v) st_visc<PREC>(gtr, tr_index(slot, v, 4, nS, side, n2, fi), Gn[v]);
   };
-  // gradient traces
+  // gradient traces (LGL, EMIT 0: none, the nodes' gradients are read instead)
   if constexpr (NODES == 1) {
-    if (act) {
+    if (EMIT == 1 && act) {
       const int idx[3] = {i, j, k};
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
@@ -506,12 +507,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
         const int side = efc_side(info), slot = efc_slot(info);
         int p = pp, qm = qq;
         if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
-        if constexpr (EMIT == 0) {
-#pragma unroll
-          for (int c = 0; c < 12; ++c) gtr[tr_index(slot, c, 12, nS, side, n2, qm * n1 + p)] = acc[c];
-        } else {
-          emit_face(info, slot, side, qm * n1 + p, q, acc);   // LGL: the node's state is its trace
-        }
+        emit_face(info, slot, side, qm * n1 + p, q, acc);   // LGL: the node's state is its trace
       }
     }
   } else {
@@ -931,7 +927,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
       if (act) {
         const int a = idx[r];
         const int pp = r == 0 ? j : i, qq = r == 2 ? j : k;
-        const double c1 = 0.5 / P.gm1;
+        const double c1 = P.c1;
         // two-point flux F#(U_a, ot) . nv
         auto two_point = [&](const Aux& ot, const double nv[3], double F[5]) {
           if (P.twopoint == 0) {

@@ -421,7 +421,7 @@ __host__ __device__ inline void surface_flux_adv(const double UL[5], const doubl
   if (FORM == 1 && P.twopoint == 0) {
     const Aux aL = logs ? make_aux_logs(qL, logs[0], logs[1]) : make_aux(qL);
     const Aux aR = logs ? make_aux_logs(qR, logs[2], logs[3]) : make_aux(qR);
-    chandrashekar<FT>(aL, aR, nv, 0.5 / P.gm1, Phi, P.p0, P.ib0);
+    chandrashekar<FT>(aL, aR, nv, P.c1, Phi, P.p0, P.ib0);
     if (aux) *aux = side ? aR : aL;
   } else {
     if (FORM == 1 && aux) *aux = make_aux(side ? qR : qL);
@@ -480,7 +480,7 @@ __host__ __device__ inline void surface_flux(const double UL[5], const double UR
 // (rho, u, p) -> U: adjoints rb, ub[3], pb of the primitive variables.
 __host__ __device__ inline void prim_vjp(const Prim& q, double gm1, double rb, const double ub[3], double pb,
                                          double Ub[5]) {
-  const double ri = 1.0 / q.rho;
+  const double ri = rcp_nr(q.rho);
   const double k = q.u[0] * q.u[0] + q.u[1] * q.u[1] + q.u[2] * q.u[2];
   Ub[4] = gm1 * pb;
   Ub[1] = ub[0] * ri - gm1 * pb * q.u[0];
@@ -490,63 +490,57 @@ __host__ __device__ inline void prim_vjp(const Prim& q, double gm1, double rb, c
 }
 
 // Adjoints of the entropy projection of the split form on Gauss nodes
-// (u~ = u(E v(U))), by forward-mode columns of the two maps: Vb += (du/dv)^T Ub
-// at the entropy variables v, and Ub += (dv/dU)^T Vb at the state U.
+// (u~ = u(E v(U))), each one reverse sweep of its map: Vb += (du/dv)^T Ub at
+// the entropy variables v, and Ub += (dv/dU)^T Vb at the state U.  (As five
+// forward-mode columns of dual numbers, each with its own exponential,
+// logarithms and divisions, they took two thirds of the instructions of the
+// N = 3 lifting adjoint.)
 __host__ __device__ inline void entropy_to_cons_vjp(const double v[5], double gm1, const double Ub[5], double Vb[5]) {
-#pragma unroll 1
-  for (int k = 0; k < 5; ++k) {
-    Dual x[5];
-#pragma unroll
-    for (int c = 0; c < 5; ++c) x[c] = Dual(v[c], c == k ? 1.0 : 0.0);
-    const Dual b = -x[4];
-    const Dual ib = Dual(1.0) / b;
-    const Dual u0 = x[1] * ib, u1 = x[2] * ib, u2 = x[3] * ib;
-    const Dual kk = u0 * u0 + u1 * u1 + u2 * u2;
-    const Dual z = x[0] + 0.5 * (b * kk);
-    const Dual rho = exp(z - (Dual(gm1 + 1.0) + log(b)) / Dual(gm1));
-    const Dual U[5] = {rho, rho * u0, rho * u1, rho * u2, rho * ib / Dual(gm1) + 0.5 * (rho * kk)};
-    double sdot = 0.0;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) sdot += Ub[c] * U[c].d;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) Vb[c] += c == k ? sdot : 0.0;
-  }
+  const double b = -v[4], ib = rcp_nr(b), igm1 = rcp_nr(gm1);
+  const double u[3] = {v[1] * ib, v[2] * ib, v[3] * ib};
+  const double k = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+  const double rho = exp(v[0] + 0.5 * b * k - (gm1 + 1.0 + log(b)) * igm1);
+  // U = (rho, rho u, rho (ib/gm1 + k/2)), ln rho = v_0 + b k/2 - (gamma + ln b)/gm1
+  const double eb = rho * Ub[4];
+  const double lrb = rho * (Ub[0] + u[0] * Ub[1] + u[1] * Ub[2] + u[2] * Ub[3]) + eb * (ib * igm1 + 0.5 * k);
+  const double kb = 0.5 * (eb + b * lrb);
+  const double ub[3] = {rho * Ub[1] + 2.0 * kb * u[0], rho * Ub[2] + 2.0 * kb * u[1], rho * Ub[3] + 2.0 * kb * u[2]};
+  // u = v_{1..3} ib, ib = 1/b
+  const double ibb = eb * igm1 + v[1] * ub[0] + v[2] * ub[1] + v[3] * ub[2];
+  Vb[0] += lrb;
+  Vb[1] += ub[0] * ib;
+  Vb[2] += ub[1] * ib;
+  Vb[3] += ub[2] * ib;
+  Vb[4] += ibb * ib * ib + (igm1 * ib - 0.5 * k) * lrb;
 }
 __host__ __device__ inline void entropy_vars_vjp(const double Uin[5], double gm1, const double Vb[5], double Ub[5]) {
-#pragma unroll 1
-  for (int k = 0; k < 5; ++k) {
-    Dual x[5];
+  const Prim q = cons2prim(Uin, gm1);
+  const double ri = rcp_nr(q.rho), pi = rcp_nr(q.p), igm1 = rcp_nr(gm1);
+  const double b = q.rho * pi, k = q.u[0] * q.u[0] + q.u[1] * q.u[1] + q.u[2] * q.u[2];
+  // v = ((gamma - s)/gm1 - b k/2, b u, -b), s = ln p - gamma ln rho, b = rho/p
+  const double bb = -0.5 * k * Vb[0] + q.u[0] * Vb[1] + q.u[1] * Vb[2] + q.u[2] * Vb[3] - Vb[4];
+  const double sb = -Vb[0] * igm1;
+  const double ub[3] = {b * (Vb[1] - q.u[0] * Vb[0]), b * (Vb[2] - q.u[1] * Vb[0]), b * (Vb[3] - q.u[2] * Vb[0])};
+  double Up[5];
+  prim_vjp(q, gm1, bb * pi - (gm1 + 1.0) * sb * ri, ub, (sb - bb * b) * pi, Up);
 #pragma unroll
-    for (int c = 0; c < 5; ++c) x[c] = Dual(Uin[c], c == k ? 1.0 : 0.0);
-    const Dual ri = Dual(1.0) / x[0];
-    const Dual u0 = x[1] * ri, u1 = x[2] * ri, u2 = x[3] * ri;
-    const Dual kk = u0 * u0 + u1 * u1 + u2 * u2;
-    const Dual p = Dual(gm1) * (x[4] - 0.5 * (x[0] * kk));
-    const Dual b = x[0] / p;
-    const Dual s = log(p) - Dual(gm1 + 1.0) * log(x[0]);
-    const Dual v[5] = {(Dual(gm1 + 1.0) - s) / Dual(gm1) - 0.5 * (b * kk), b * u0, b * u1, b * u2, -b};
-    double sdot = 0.0;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) sdot += Vb[c] * v[c].d;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) Ub[c] += c == k ? sdot : 0.0;
-  }
+  for (int c = 0; c < 5; ++c) Ub[c] += Up[c];
 }
 
-// Adjoint of Roe's dissipation D(UL, UR) on the unit normal nh: ULb, URb +=
-// (dD/dU)^T Db, one forward-mode column per entry of UL and UR (primitives by
-// the operations of cons2prim).
+// Adjoint of Roe's dissipation D(UL, UR) on the unit normal nh with respect to
+// the state of one side (0: UL, 1: UR): Ub += (dD/dU_side)^T Db, one
+// forward-mode column per entry (primitives by the operations of cons2prim).
 __host__ __device__ inline void roe_dissipation_vjp(const double UL[5], const double UR[5], const double nh[3],
-                                                    const Phys& P, const double Db[5], double ULb[5], double URb[5]) {
+                                                    const Phys& P, const double Db[5], int side, double Ub[5]) {
   const Dual gam(P.gamma);
   const Dual n[3] = {Dual(nh[0]), Dual(nh[1]), Dual(nh[2])};
 #pragma unroll 1
-  for (int k = 0; k < 10; ++k) {
+  for (int k = 0; k < 5; ++k) {
     Dual uL[5], uR[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      uL[v] = Dual(UL[v], k == v ? 1.0 : 0.0);
-      uR[v] = Dual(UR[v], k == 5 + v ? 1.0 : 0.0);
+      uL[v] = Dual(UL[v], side == 0 && k == v ? 1.0 : 0.0);
+      uR[v] = Dual(UR[v], side == 1 && k == v ? 1.0 : 0.0);
     }
     const Dual riL = Dual(1.0) / uL[0], riR = Dual(1.0) / uR[0];
     const Dual ul[3] = {uL[1] * riL, uL[2] * riL, uL[3] * riL}, ur[3] = {uR[1] * riR, uR[2] * riR, uR[3] * riR};
@@ -558,18 +552,15 @@ __host__ __device__ inline void roe_dissipation_vjp(const double UL[5], const do
     double sdot = 0.0;
 #pragma unroll
     for (int v = 0; v < 5; ++v) sdot += Db[v] * D[v].d;
-    // (selects, not a run-time index, keep ULb and URb in registers)
+    // (selects, not a run-time index, keep Ub in registers)
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      ULb[v] += k == v ? sdot : 0.0;
-      URb[v] += k == 5 + v ? sdot : 0.0;
-    }
+    for (int v = 0; v < 5; ++v) Ub[v] += k == v ? sdot : 0.0;
   }
 }
 
 // Adjoint of the lifted variables q = (u, v, w, T = p/(rho R)).
 __host__ __device__ inline void qvars_vjp(const Prim& q, double gm1, double Rinv, const double qb[4], double Ub[5]) {
-  const double ri = 1.0 / q.rho;
+  const double ri = rcp_nr(q.rho);
   const double T = q.p * ri * Rinv;
   const double pb = qb[3] * ri * Rinv;
   const double rb = -qb[3] * T * ri;
@@ -582,9 +573,11 @@ struct AuxBar {
 };
 
 __host__ __device__ inline void aux_vjp(const Prim& q, const Aux& a, const AuxBar& b, double gm1, double Ub[5]) {
-  const double betab = b.beta + b.lbeta / a.beta;
-  double rb = b.rho + b.lrho / a.rho + betab * 0.5 / q.p;
-  const double pb = -betab * a.beta / q.p;
+  // (1/beta = 2 p/rho)
+  const double ri = rcp_nr(q.rho), pi = rcp_nr(q.p);
+  const double betab = b.beta + b.lbeta * 2.0 * q.p * ri;
+  double rb = b.rho + b.lrho * ri + betab * 0.5 * pi;
+  const double pb = -betab * a.beta * pi;
   const double ub[3] = {b.u[0] + 2.0 * q.u[0] * b.k, b.u[1] + 2.0 * q.u[1] * b.k, b.u[2] + 2.0 * q.u[2] * b.k};
   prim_vjp(q, gm1, rb, ub, pb, Ub);
 }
@@ -801,73 +794,80 @@ __host__ __device__ inline void viscous_flux_vjp(const Prim& q, const double g[1
   viscous_tensor_vjp<VL>(q, g, P, M, gb, ub, rpb);
 }
 
-// Adjoint of the surface flux (FP64): ULb, URb, and for Navier-Stokes gLb, gRb.
+// Adjoint of the surface flux (FP64) with respect to one side's own inputs:
+// Uo and Un are the states of that side and of the other, side which of the
+// two is the master's (0: Uo is UL, 1: Uo is UR); Ub receives the adjoint of Uo
+// and, for Navier-Stokes, gb that of its gradient go.  Each element needs its
+// own side only, and the viscous part of a side depends on that side's state
+// and gradient alone, so the other side's gradient is not an input.
 // ROE 1: Roe's dissipation; VL 1: Sutherland's law (compile-time choices,
 // as in the residual).
 template <int FORM, int PHYS, int ROE = 0, int VL = 0>
-__host__ __device__ inline void surface_flux_vjp(const double UL[5], const double UR[5], const double* gL,
-                                                 const double* gR, const double nh[3], double s, const Phys& P,
-                                                 const double Phib[5], double ULb[5], double URb[5], double* gLb,
-                                                 double* gRb) {
-  const Prim qL = cons2prim(UL, P.gm1), qR = cons2prim(UR, P.gm1);
+__host__ __device__ inline void surface_flux_vjp_own(const double Uo[5], const double Un[5], const double* go,
+                                                     int side, const double nh[3], double s, const Phys& P,
+                                                     const double Phib[5], double Ub[5], double* gb) {
+  const Prim qo = cons2prim(Uo, P.gm1), qn = cons2prim(Un, P.gm1);
   const double nv[3] = {nh[0] * s, nh[1] * s, nh[2] * s};
-  // central part
+  // central part (both two-point fluxes are symmetric in their states)
   if (FORM == 0 || P.twopoint == 1) {
     const double wh[5] = {0.5 * Phib[0], 0.5 * Phib[1], 0.5 * Phib[2], 0.5 * Phib[3], 0.5 * Phib[4]};
-    euler_flux_vjp(UL, qL, nv, wh, P.gm1, ULb);
-    euler_flux_vjp(UR, qR, nv, wh, P.gm1, URb);
+    euler_flux_vjp(Uo, qo, nv, wh, P.gm1, Ub);
   } else {
-    const Aux aL = make_aux(qL), aR = make_aux(qR);
-    AuxBar bL, bR;
-    chandrashekar_vjp_ab(aL, aR, nv, 0.5 / P.gm1, Phib, bL, bR);
-    aux_vjp(qL, aL, bL, P.gm1, ULb);
-    aux_vjp(qR, aR, bR, P.gm1, URb);
+    const Aux ao = make_aux(qo), an = make_aux(qn);
+    AuxBar bo;
+    chandrashekar_vjp_a(ao, an, nv, P.c1, Phib, bo);
+    aux_vjp(qo, ao, bo, P.gm1, Ub);
   }
   // Roe's dissipation: Phi -= (s/2) D(UL, UR)
   if constexpr (ROE == 1) {
     const double Db[5] = {-0.5 * s * Phib[0], -0.5 * s * Phib[1], -0.5 * s * Phib[2], -0.5 * s * Phib[3],
                           -0.5 * s * Phib[4]};
-    roe_dissipation_vjp(UL, UR, nh, P, Db, ULb, URb);
+    double UL[5], UR[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) { UL[v] = side ? Un[v] : Uo[v]; UR[v] = side ? Uo[v] : Un[v]; }
+    roe_dissipation_vjp(UL, UR, nh, P, Db, side, Ub);
   }
-  // Rusanov dissipation
+  // Rusanov dissipation: Phi -= (s/2) lmax (UR - UL); the own side's wave speed
+  // matters where it is the larger one (ties: the master's)
   if (ROE == 0 && P.riemann == 0) {
-    const double cL = sqrt(P.gamma * qL.p / qL.rho), cR = sqrt(P.gamma * qR.p / qR.rho);
-    const double unL = qL.u[0] * nh[0] + qL.u[1] * nh[1] + qL.u[2] * nh[2];
-    const double unR = qR.u[0] * nh[0] + qR.u[1] * nh[1] + qR.u[2] * nh[2];
-    const double lL = fabs(unL) + cL, lR = fabs(unR) + cR;
-    const bool left = lL >= lR;
-    const double lmax = left ? lL : lR;
-    const double hs = 0.5 * (lmax * s);
+    const double ro = rcp_nr(qo.rho);
+    const double co = sqrt(P.gamma * qo.p * ro), cn = sqrt(P.gamma * qn.p * rcp_nr(qn.rho));
+    const double uno = qo.u[0] * nh[0] + qo.u[1] * nh[1] + qo.u[2] * nh[2];
+    const double unn = qn.u[0] * nh[0] + qn.u[1] * nh[1] + qn.u[2] * nh[2];
+    const double lo = fabs(uno) + co, ln = fabs(unn) + cn;
+    const bool mine = side ? !(ln >= lo) : lo >= ln;
+    const double hs = (side ? -0.5 : 0.5) * ((mine ? lo : ln) * s);
     double lb = 0.0;
     for (int v = 0; v < 5; ++v) {
-      URb[v] -= hs * Phib[v];
-      ULb[v] += hs * Phib[v];
-      lb -= 0.5 * s * Phib[v] * (UR[v] - UL[v]);
+      Ub[v] += hs * Phib[v];
+      lb += Phib[v] * (Uo[v] - Un[v]);
     }
-    const Prim& qa = left ? qL : qR;
-    const double una = left ? unL : unR;
-    const double ca = left ? cL : cR;
-    const double sg = una >= 0.0 ? 1.0 : -1.0;
-    const double ub[3] = {lb * sg * nh[0], lb * sg * nh[1], lb * sg * nh[2]};
-    const double cb = lb;
-    const double pb = cb * P.gamma / (2.0 * ca * qa.rho);
-    const double rb = -cb * P.gamma * qa.p / (2.0 * ca * qa.rho * qa.rho);
-    double Ub[5];
-    prim_vjp(qa, P.gm1, rb, ub, pb, Ub);
-    double* tgt = left ? ULb : URb;
-    for (int v = 0; v < 5; ++v) tgt[v] += Ub[v];
+    lb *= mine ? (side ? -0.5 : 0.5) * s : 0.0;
+    const double sg = uno >= 0.0 ? lb : -lb;
+    const double ub[3] = {sg * nh[0], sg * nh[1], sg * nh[2]};
+    const double pb = lb * P.gamma * ro * 0.5 * rcp_nr(co);
+    double Up[5];
+    prim_vjp(qo, P.gm1, -pb * qo.p * ro, ub, pb, Up);
+    for (int v = 0; v < 5; ++v) Ub[v] += Up[v];
   }
   if constexpr (PHYS == 1) {
     const double Gnb[4] = {-0.5 * Phib[1], -0.5 * Phib[2], -0.5 * Phib[3], -0.5 * Phib[4]};
-    double ubL[3], ubR[3], rpL[2] = {0.0, 0.0}, rpR[2] = {0.0, 0.0};
-    viscous_flux_vjp<VL>(qL, gL, P, nv, Gnb, gLb, ubL, rpL);
-    viscous_flux_vjp<VL>(qR, gR, P, nv, Gnb, gRb, ubR, rpR);
-    double Ub[5];
-    prim_vjp(qL, P.gm1, rpL[0], ubL, rpL[1], Ub);
-    for (int v = 0; v < 5; ++v) ULb[v] += Ub[v];
-    prim_vjp(qR, P.gm1, rpR[0], ubR, rpR[1], Ub);
-    for (int v = 0; v < 5; ++v) URb[v] += Ub[v];
+    double ub[3], rp[2] = {0.0, 0.0};
+    viscous_flux_vjp<VL>(qo, go, P, nv, Gnb, gb, ub, rp);
+    double Up[5];
+    prim_vjp(qo, P.gm1, rp[0], ub, rp[1], Up);
+    for (int v = 0; v < 5; ++v) Ub[v] += Up[v];
   }
+}
+
+// Adjoint of the surface flux with respect to both sides.
+template <int FORM, int PHYS, int ROE = 0, int VL = 0>
+__host__ __device__ inline void surface_flux_vjp(const double UL[5], const double UR[5], const double* gL,
+                                                 const double* gR, const double nh[3], double s, const Phys& P,
+                                                 const double Phib[5], double ULb[5], double URb[5], double* gLb,
+                                                 double* gRb) {
+  surface_flux_vjp_own<FORM, PHYS, ROE, VL>(UL, UR, gL, 0, nh, s, P, Phib, ULb, gLb);
+  surface_flux_vjp_own<FORM, PHYS, ROE, VL>(UR, UL, gR, 1, nh, s, P, Phib, URb, gRb);
 }
 
 }  // namespace dgx
