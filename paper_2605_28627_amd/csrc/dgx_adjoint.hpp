@@ -38,7 +38,7 @@ __device__ __forceinline__ double adj_store(const AdjUpd& up, double* out, size_
 // Per-element surface adjoint t = -(1/w_a) l_a(+-1) (sJ lam)_a summed along
 // the normal line, from sl = sJ lam [5][n3] in LDS (the element's nodes).
 template <int N, int NODES>
-__device__ inline void adj_surface_of(const Geo& G, const DevBasis& sb, const double* sl, int e, int t,
+__device__ inline void adj_surface_of(const Geo& G, const VolBasis<N>& sb, const double* sl, int e, int t,
                                       double* __restrict__ Lbar) {
   using S = Shape<N>;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
@@ -71,15 +71,17 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_adj_trace(Geo G, const double
   using S = Shape<N>;
   constexpr int n3 = S::n3;
   __shared__ double sl[5 * n3];
-  __shared__ DevBasis sb;
+  __shared__ VolBasis<N> sb;
   const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems;
-  load_basis(&sb, G.basis, t, S::nth);
+  BasisCopy<N, false, S::nth> bc;
+  bc.load(G.basis, t);
   if (t < n3) {
     const double sJ = node_metric(G, e, n3, t).sj();
 #pragma unroll
     for (int v = 0; v < 5; ++v) sl[v * n3 + t] = sJ * lam[((size_t)v * nE + e) * n3 + t];
   }
+  bc.store(&sb, t);
   __syncthreads();
   adj_surface_of<N, NODES>(G, sb, sl, e, t, Lbar);
 }
@@ -142,10 +144,11 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
   __shared__ double sB[SZ_B];     // surface adjoints, then aux + metric row
   __shared__ double sw[kW ? 12 * n3 : 1];
   __shared__ double sub[ES ? 5 * S::nface : 1];   // ES: adjoints of the own projected traces
-  __shared__ DevBasis sb;
+  __shared__ VolBasis<N> sb;
   const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems, nS = G.nSides;
-  load_basis(&sb, G.basis, t, S::nth);
+  BasisCopy<N, false, S::nth> bc;
+  bc.load(G.basis, t);
   const bool act = t < n3;
   const int i = t % n1, j = (t / n1) % n1, k = t / n2;
   const int idx[3] = {i, j, k};
@@ -238,6 +241,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
       for (int c = 0; c < 12; ++c) sB[(f * NF + 5 + c) * n2 + rr] = gob[c];
     }
   }
+  bc.store(&sb, t);
   __syncthreads();
   double Ub[5] = {0, 0, 0, 0, 0};
   double gb[PHYS == 1 ? 12 : 1];
@@ -675,16 +679,16 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_adj_lift_volume(Geo G, Phys P
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
   constexpr int SZ = 5 * S::nface > 5 * n3 ? 5 * S::nface : 5 * n3;
   __shared__ double sm[SZ];
-  __shared__ DevBasis sb;
+  __shared__ VolBasis<N> sb;
   const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems, nS = G.nSides;
-  load_basis(&sb, G.basis, t, S::nth);
+  BasisCopy<N, false, S::nth> bc;
+  bc.load(G.basis, t);
   const bool act = t < n3;
   const int i = t % n1, j = (t / n1) % n1, k = t / n2;
   const int idx[3] = {i, j, k};
   const double sJ = act ? node_metric(G, e, n3, t).sj() : 0.0;
   double Ub[5] = {0, 0, 0, 0, 0};
-  __syncthreads();
   double* sfb = sm;  // [6][5][n2]
   for (int ft = t; ft < S::nface; ft += S::nth) {
     const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1;
@@ -711,6 +715,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_adj_lift_volume(Geo G, Phys P
 #pragma unroll
     for (int v = 0; v < 5; ++v) sfb[(f * 5 + v) * n2 + rr] = Ut[v];
   }
+  bc.store(&sb, t);
   __syncthreads();
   if (act) {
     double Fb[5] = {0, 0, 0, 0, 0};   // the faces' part (EP: of the node's entropy variables)

@@ -207,11 +207,12 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_trace_fv(Geo G, Phys P, const
   __shared__ double sa[5 * n3];
   __shared__ double sb2[5 * n3];
   __shared__ double sBs[n1 * n1];
-  __shared__ DevBasis sbb;
+  __shared__ VolBasis<N> sbb;
   const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems, nS = G.nSides;
   const bool act = t < n3;
-  load_basis(&sbb, G.basis, t, S::nth);
+  BasisCopy<N, false, S::nth> bc;
+  bc.load(G.basis, t);
   for (int x = t; x < n1 * n1; x += S::nth) sBs[x] = G.basis->Bs[x];
   const int efl = G.efv[e];        // bits 0..5: FV faces, bit 6: FV element
   const int et = (efl >> 6) & 1;
@@ -223,6 +224,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_trace_fv(Geo G, Phys P, const
 #pragma unroll
     for (int v = 0; v < 5; ++v) snod[v * n3 + t] = u[v];
   }
+  bc.store(&sbb, t);
   __syncthreads();
   if (anyfv) {
     // primitive means of every sub-cell into sb2

@@ -396,6 +396,9 @@ dg_status dg_create(const dg_config* cfg, dg_ctx** out) {
     }
   }
   if (c.fv) fv_operators(n1, x->x, b);
+  double* pk = b.packed;
+  for (const double* v : {b.winv, b.Lm, b.Lp}) pk = std::copy(v, v + n1, pk);
+  for (const double* v : {b.Dhat, b.DS, b.Bs, b.Bsi}) pk = std::copy(v, v + n1 * n1, pk);
   *out = x;
   return DG_OK;
 }

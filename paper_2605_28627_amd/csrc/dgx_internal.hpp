@@ -25,6 +25,8 @@ struct DevBasis {
   double Bs[kMaxN1 * kMaxN1];     // Bs[k*n1+i] = integral of l_i over sub-interval k of [-1,1]
   double Bsi[kMaxN1 * kMaxN1];    // inverse of Bs
   double Vli[kMaxN1 * kMaxN1];    // inverse of the orthonormal-Legendre Vandermonde V[i*n1+m] = P~_m(x_i)
+  // winv, Lm, Lp (n1 each), Dhat, DS, Bs, Bsi (n1^2 each) one behind the other
+  double packed[3 * kMaxN1 + 4 * kMaxN1 * kMaxN1];
 };
 
 // Per-element face table entry: side index (27 bits), slot (0 master /

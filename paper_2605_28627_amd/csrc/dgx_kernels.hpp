@@ -26,25 +26,6 @@
 
 namespace dgx {
 
-// The entries of the basis the residual and lifting kernels read, at their
-// exact size (the LDS footprint decides how many elements share a CU).
-// (FVB: also the FV sub-cell operators Bs, Bs^-1.)
-template <int N, bool FVB = false>
-struct VolBasis {
-  static constexpr int n1 = N + 1;
-  static constexpr int nf = FVB ? n1 * n1 : 1;
-  double winv[n1], Lm[n1], Lp[n1], Dhat[n1 * n1], DS[n1 * n1], Bs[nf], Bsi[nf];
-};
-template <int N, bool FVB = false>
-__device__ __forceinline__ void load_vol_basis(VolBasis<N, FVB>* dst, const DevBasis* src, int t, int nth) {
-  constexpr int n1 = N + 1;
-  for (int x = t; x < n1; x += nth) { dst->winv[x] = src->winv[x]; dst->Lm[x] = src->Lm[x]; dst->Lp[x] = src->Lp[x]; }
-  for (int x = t; x < n1 * n1; x += nth) { dst->Dhat[x] = src->Dhat[x]; dst->DS[x] = src->DS[x]; }
-  if constexpr (FVB)
-    for (int x = t; x < n1 * n1; x += nth) { dst->Bs[x] = src->Bs[x]; dst->Bsi[x] = src->Bsi[x]; }
-}
-
-
 // ---------------------------------------------------------------------------
 // Trace kernel: U at the element faces -> Utr[slot][5][side][master (p,q)].
 // EP 1 (split form on Gauss nodes): the entropy-projected trace u(E v(U)),
@@ -81,8 +62,14 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_trace(Geo G, Phys P, const do
     }
   } else {
     __shared__ double su[5 * n3];
-    __shared__ DevBasis sb;
-    load_basis(&sb, G.basis, t, S::nth);
+    __shared__ VolBasis<N> sb;
+    BasisCopy<N, false, S::nth> bc;
+    bc.load(G.basis, t);
+    // the face table entries of this work-item's face nodes
+    constexpr int kFI = (S::nface + S::nth - 1) / S::nth;
+    int finfo[kFI];
+#pragma unroll
+    for (int it = 0; it < kFI; ++it) finfo[it] = t + it * S::nth < S::nface ? G.efc[e * 6 + face_of<N>(t + it * S::nth)] : 0;
     if (t < n3) {
       double u[5];
 #pragma unroll
@@ -97,11 +84,15 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_trace(Geo G, Phys P, const do
         for (int v = 0; v < 5; ++v) su[v * n3 + t] = u[v];
       }
     }
+    bc.store(&sb, t);
     __syncthreads();
-    for (int ft = t; ft < S::nface; ft += S::nth) {
-      const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
+#pragma unroll
+    for (int it = 0; it < kFI; ++it) {
+      const int ft = t + it * S::nth;
+      if (ft >= S::nface) break;
+      const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
       const double* L = (f & 1) ? sb.Lp : sb.Lm;
-      const int info = G.efc[e * 6 + f];
+      const int info = finfo[it];
       const int side = efc_side(info), slot = efc_slot(info);
       int p = pp, q = qq;
       if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, q);
@@ -194,7 +185,12 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
   if (kFvf && !(efl & 63)) return;       // (no FV face: the FV 3 variant)
   if (FV == 3 && (efl & 63)) return;
   const int nE = G.nElems, nS = G.nSides;
-  load_vol_basis<N, kFvf>(&sb, G.basis, t, S::nth);
+  BasisCopy<N, kFvf, S::nth> bc;
+  bc.load(G.basis, t);
+  constexpr int kFI = (S::nface + S::nth - 1) / S::nth;
+  int finfo[kFI];   // the face table entries of this work-item's face nodes
+#pragma unroll
+  for (int it = 0; it < kFI; ++it) finfo[it] = t + it * S::nth < S::nface ? G.efc[e * 6 + face_of<N>(t + it * S::nth)] : 0;
   double* sq = sm;            // [4][n3]
   double* sja = sm + 4 * n3;  // [9][n3]
   const bool act = t < n3;
@@ -228,9 +224,8 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
 #pragma unroll
     for (int c = 0; c < 3; ++c) sf[(f * 7 + 4 + c) * n2 + rr] = sgn * (nsf[c] * nsf[3]);
   };
-  auto face_load = [&](int ft, int& slot, double UO[5], double UR[5], double nsf[4]) {
-    const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1;
-    const int info = G.efc[e * 6 + f];
+  auto face_load = [&](int ft, int info, int& slot, double UO[5], double UR[5], double nsf[4]) {
+    const int rr = ft % n2, pp = rr % n1, qq = rr / n1;
     const int side = efc_side(info);
     slot = efc_slot(info);
     int p = pp, qm = qq;
@@ -266,7 +261,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
     sJ = nm.sj();
   }
   if constexpr (kOneFaceNode && !kFvf) {
-    if (t < S::nface) face_load(t, fslot, fUL, fUR, fns);
+    if (t < S::nface) face_load(t, finfo[0], fslot, fUL, fUR, fns);
   }
   if (act) {
     if constexpr (FV == 1 && NODES == 0) {
@@ -286,6 +281,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
 #pragma unroll
     for (int c = 0; c < 9; ++c) sja[c * n3 + t] = jl[c];
   }
+  bc.store(&sb, t);
   // LGL: the face averages read the own q tile (FV contexts: and the own state)
   if constexpr (NODES == 1 || kFvf) __syncthreads();
   if constexpr (kFvf) {
@@ -297,7 +293,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
       if (!((efl >> f) & 1)) {
         int slot;
         double UL[5], UR[5], nsf[4];
-        face_load(ft, slot, UL, UR, nsf);
+        face_load(ft, G.efc[e * 6 + f], slot, UL, UR, nsf);
         face_avg(ft, slot, UL, UR, nsf);
         continue;
       }
@@ -362,10 +358,13 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
   } else if constexpr (kOneFaceNode) {
     if (t < S::nface) face_avg(t, fslot, fUL, fUR, fns);
   } else {
-    for (int ft = t; ft < S::nface; ft += S::nth) {
+#pragma unroll
+    for (int it = 0; it < kFI; ++it) {
+      const int ft = t + it * S::nth;
+      if (ft >= S::nface) break;
       int slot;
       double UL[5], UR[5], nsf[4];
-      face_load(ft, slot, UL, UR, nsf);
+      face_load(ft, finfo[it], slot, UL, UR, nsf);
       face_avg(ft, slot, UL, UR, nsf);
     }
   }
@@ -516,11 +515,14 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
 #pragma unroll
       for (int c = 0; c < 12; ++c) sm[c * n3 + t] = acc[c];
     __syncthreads();
-    for (int ft = t; ft < S::nface; ft += S::nth) {
-      const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
+#pragma unroll
+    for (int it = 0; it < kFI; ++it) {
+      const int ft = t + it * S::nth;
+      if (ft >= S::nface) break;
+      const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
       if (kFvf && ((efl >> f) & 1)) continue;
       const double* L = (f & 1) ? sb.Lp : sb.Lm;
-      const int info = G.efc[e * 6 + f];
+      const int info = finfo[it];
       const int side = efc_side(info), slot = efc_slot(info);
       int p = pp, qm = qq;
       if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
@@ -709,7 +711,12 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
   if (FV == 1 && PHYS == 1 && !(efl & 63)) return;
   if (FV == 2 && (efl & 63)) return;
   const int nE = G.nElems, nS = G.nSides;
-  load_vol_basis<N, kFvf>(&sb, G.basis, t, S::nth);
+  BasisCopy<N, kFvf, S::nth> bc;
+  bc.load(G.basis, t);
+  constexpr int kFI = (S::nface + S::nth - 1) / S::nth;
+  int finfo[kFI];   // the face table entries of this work-item's face nodes
+#pragma unroll
+  for (int it = 0; it < kFI; ++it) finfo[it] = t + it * S::nth < S::nface ? G.efc[e * 6 + face_of<N>(t + it * S::nth)] : 0;
   const bool act = t < n3;
   const int i = t % n1, j = (t / n1) % n1, k = t / n2;
   const int idx[3] = {i, j, k};
@@ -763,9 +770,8 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
     fetch_dir(0);
   }
   // surface flux of face f at its node rr into LDS slot fs (and, ES, the own record)
-  auto face_node = [&](int f, int rr, int fs) {
+  auto face_node = [&](int f, int info, int rr, int fs) {
     const int pp = rr % n1, qq = rr / n1;
-    const int info = G.efc[e * 6 + f];
     const int side = efc_side(info), slot = efc_slot(info);
     int p = pp, qm = qq;
     if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
@@ -822,11 +828,15 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
   };
   // 1. surface fluxes of the six faces (other forms)
   if constexpr (!ES) {
-    for (int ft = t; ft < S::nface; ft += S::nth) {
+#pragma unroll
+    for (int it = 0; it < kFI; ++it) {
+      const int ft = t + it * S::nth;
+      if (ft >= S::nface) break;
       const int f = face_of<N>(ft);
-      face_node(f, ft % n2, f);
+      face_node(f, finfo[it], ft % n2, f);
     }
   }
+  bc.store(&sb, t);
   if constexpr (ES && kFvf) {
     if (efl & 63) {
       // FV faces of the Gauss split form: the traces there hold sub-cell
@@ -860,7 +870,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
       }
       __syncthreads();
       for (int ft = t; ft < S::nface; ft += S::nth)
-        if ((efl >> (ft / n2)) & 1) face_node(ft / n2, ft % n2, ft / n2);
+        if ((efl >> (ft / n2)) & 1) face_node(ft / n2, G.efc[e * 6 + ft / n2], ft % n2, ft / n2);
     }
   }
   if constexpr (kFvf) {
@@ -911,7 +921,8 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
         constexpr int fa[3] = {0, 6, 4}, fb[3] = {4, 6, 6};
         for (int ft = fa[r] * n2 + t; ft < fb[r] * n2; ft += S::nth) {
           if (kFvf && ((efl >> (ft / n2)) & 1)) continue;   // formed in step 1
-          face_node(ft / n2, ft % n2, kFvf ? ft / n2 : es_face_slot(ft / n2));
+          const int f = face_of<N>(ft);
+          face_node(f, G.efc[e * 6 + f], ft % n2, kFvf ? f : es_face_slot(f));
         }
       }
       if (act) {
@@ -1182,10 +1193,13 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
         for (int v = 0; v < 5; ++v) sm[v * n3 + t] = w[v];
       }
       __syncthreads();
-      for (int ft = t; ft < S::nface; ft += S::nth) {
-        const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
+#pragma unroll
+      for (int it = 0; it < kFI; ++it) {
+        const int ft = t + it * S::nth;
+        if (ft >= S::nface) break;
+        const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
         const double* L = (f & 1) ? sb.Lp : sb.Lm;
-        const int info = G.efc[e * 6 + f];
+        const int info = finfo[it];
         const int side = efc_side(info), slot = efc_slot(info);
         if (kFvf && ((efl >> f) & 1)) continue;
         int p = pp, qm = qq;

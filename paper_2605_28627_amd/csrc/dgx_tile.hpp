@@ -21,19 +21,48 @@ struct Shape {
 template <int N>
 __device__ __forceinline__ int nidx(int i, int j, int k) { return (k * (N + 1) + j) * (N + 1) + i; }
 
-// Volume node at position a along reference direction r, tangential face indices (pp, qq).
+// Volume node at position a along reference direction r, tangential face
+// indices (pp, qq).  One stride per index, chosen by r: where r differs between
+// lanes (face loops) that is three selects per line; a choice between three
+// node formulas became two branches for every node of the line (the trace loop
+// of an N = 3 Gauss element: 40 branches instead of 20 LDS reads in a row).
 template <int N>
 __device__ __forceinline__ int line_node(int r, int a, int pp, int qq) {
-  return r == 0 ? nidx<N>(a, pp, qq) : (r == 1 ? nidx<N>(pp, a, qq) : nidx<N>(pp, qq, a));
+  constexpr int n1 = N + 1, n2 = n1 * n1;
+  return pp * (r == 0 ? n1 : 1) + qq * (r == 2 ? n1 : n2) + a * (r == 0 ? 1 : (r == 1 ? n1 : n2));
 }
 
-// Copy the basis into LDS (cooperatively).
-__device__ __forceinline__ void load_basis(DevBasis* dst, const DevBasis* src, int t, int nth) {
-  const double* s = reinterpret_cast<const double*>(src);
-  double* d = reinterpret_cast<double*>(dst);
-  constexpr int nd = sizeof(DevBasis) / sizeof(double);
-  for (int x = t; x < nd; x += nth) d[x] = s[x];
-}
+// The entries of the basis the kernels read, at their exact size (the LDS
+// footprint decides how many elements share a CU), in the order of
+// DevBasis::packed.  (FVB: also the FV sub-cell operators Bs, Bs^-1.)
+template <int N, bool FVB = false>
+struct VolBasis {
+  static constexpr int n1 = N + 1;
+  static constexpr int nf = FVB ? n1 * n1 : 1;
+  static constexpr int nd = 3 * n1 + 2 * n1 * n1 + (FVB ? 2 * n1 * n1 : 0);   // doubles copied
+  double winv[n1], Lm[n1], Lp[n1], Dhat[n1 * n1], DS[n1 * n1], Bs[nf], Bsi[nf];
+};
+
+// The basis copy in two parts, so that its loads are in flight together with
+// the element's own and nothing waits for them alone: load() at the start of a
+// kernel, store() to LDS before the first barrier.  At most one value per
+// work-item (FVB, N = 3: two); loaded array by array and stored at once it cost
+// every workgroup two memory latencies before its first load of the state.
+template <int N, bool FVB, int NTH>
+struct BasisCopy {
+  static constexpr int nd = VolBasis<N, FVB>::nd, k = (nd + NTH - 1) / NTH;
+  double v[k];
+  __device__ __forceinline__ void load(const DevBasis* src, int t) {
+#pragma unroll
+    for (int i = 0; i < k; ++i) v[i] = t + i * NTH < nd ? src->packed[t + i * NTH] : 0.0;
+  }
+  __device__ __forceinline__ void store(VolBasis<N, FVB>* dst, int t) const {
+    double* d = reinterpret_cast<double*>(dst);
+#pragma unroll
+    for (int i = 0; i < k; ++i)
+      if (t + i * NTH < nd) d[t + i * NTH] = v[i];
+  }
+};
 
 // Where node t of element e finds its metric terms: component c (Ja^r_n at
 // c = 3r+n, 1/J at c = 9) at base[off + c st].  Both stores are [10][...]:
