@@ -741,10 +741,16 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
     else
       sJn = G.sJ[(size_t)e * n3 + t];
     if constexpr (MODE == 1) {
+      // The first LSERK stage has A = 0 and must not see dU: the split form
+      // skips the read; the weak form, which fetches two directions ahead, reads
+      // the own state's cache lines instead (the update drops the value), since
+      // behind a branch around the loads the next direction's waits cover them
+      // too (5 % of a step on meshes too small to fill the chip).
+      const double* dsrc = A != 0.0 ? dU : U;
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         const size_t gi = ((size_t)v * nE + e) * n3 + t;
-        dUn[v] = A != 0.0 ? dU[gi] : 0.0;   // the first LSERK stage has A = 0: no read
+        dUn[v] = FORM == 0 ? dsrc[gi] : (A != 0.0 ? dU[gi] : 0.0);
         if constexpr (FORM == 1) Un[v] = U[gi];
       }
     }
@@ -1157,7 +1163,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         const size_t gi = ((size_t)v * nE + e) * n3 + t;
-        const double d = A * dUn[v] + dt * (acc[v] * sJ);
+        const double d = A * (FORM == 1 || A != 0.0 ? dUn[v] : 0.0) + dt * (acc[v] * sJ);
         dU[gi] = d;
         Unew[v] = (FORM == 1 ? Un[v] : u[v]) + B * d;
         Uio[gi] = Unew[v];
