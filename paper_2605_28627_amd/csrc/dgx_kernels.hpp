@@ -797,10 +797,23 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
       }
     }
     double UL[5], UR[5];
+    if constexpr (NODES == 1) {
+      // LGL: the own trace is the face node's state, read from U (the element's
+      // own loads' cache lines, and no trip through the face table) instead of
+      // the traces: 30 B per node less at N = 7.  The bits are the trace's.
+      const double* un = U + (size_t)e * n3 + line_node<N>(f / 2, (f & 1) ? N : 0, pp, qq);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      UL[v] = Utr[tr_index(0, v, TNV, nS, side, n2, fi)];
-      UR[v] = Utr[tr_index(1, v, TNV, nS, side, n2, fi)];
+      for (int v = 0; v < 5; ++v) {
+        const double uo = un[(size_t)v * nE * n3], ut = Utr[tr_index(1 - slot, v, TNV, nS, side, n2, fi)];
+        UL[v] = slot ? ut : uo;
+        UR[v] = slot ? uo : ut;
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        UL[v] = Utr[tr_index(0, v, TNV, nS, side, n2, fi)];
+        UR[v] = Utr[tr_index(1, v, TNV, nS, side, n2, fi)];
+      }
     }
     const FaceGeom fg = face_geom(G, info, n2, fi);
     const double nh[3] = {fg(0), fg(1), fg(2)};
