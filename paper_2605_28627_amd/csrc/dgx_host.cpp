@@ -971,6 +971,7 @@ static Cfg kcfg(const dg_ctx* c) {
   k.roe = c->cfg.riemann == DG_RIEMANN_ROE ? 1 : 0;
   k.visc = c->cfg.viscosity == DG_VISC_SUTHERLAND ? 1 : 0;
   k.fv = c->cfg.fv;
+  k.affine = c->n_const_metric == c->nElems;
   return k;
 }
 

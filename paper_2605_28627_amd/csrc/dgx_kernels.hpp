@@ -659,7 +659,16 @@ constexpr int volume_waves() {
 // primitive traces there.  Navier-Stokes: those sub-face fluxes subtract the mean of
 // both layer-0 sub-cells' viscous fluxes, from the gradients at
 // gvf + 8 nSides n2.
-template <int N, int NODES, int FORM, int PHYS, int PREC, int MODE, int ROE, int FV = 0>
+//
+// AFF 1 (split form, every element of the mesh affine, Chandrashekar's flux):
+// the metric terms are uniform over the workgroup and live in scalar
+// registers; no metric rows in LDS (N = 7: 12 KB), none read per pair, and no
+// barriers between directions whose pairs stay inside a wavefront.  The
+// central two-point flux is compiled out of the pair loops, where it cost 10-20
+// registers as a run-time choice.  N = 7 Navier-Stokes: 105 VGPRs and 66 KB
+// instead of 122 and 78; 32^3 (2 steps) 23.2 -> 22.5 ms, 16^3 (4 steps)
+// 5.87 -> 5.57 ms, N = 5 Euler 20^3 3.76 -> 3.25 ms.
+template <int N, int NODES, int FORM, int PHYS, int PREC, int MODE, int ROE, int FV = 0, int AFF = 0>
 __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) void k_volume(Geo G, Phys P, const double* __restrict__ U,
                                                           const double* __restrict__ Utr,
                                                           const double* __restrict__ gvn,
@@ -680,7 +689,8 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
   constexpr bool kEsAllShfl = kSymLines && n1 == 4;
   // the two-point record of every node (7 values; |u|^2 is recomputed from u)
   constexpr int kAuxV = 7;
-  constexpr int SZ_SPLIT = (kAuxV + 3 + (ES && !kEsAllShfl ? 10 : 0)) * n3;   // aux + Ja^r (+ face coupling)
+  constexpr int kJaV = AFF ? 0 : 3;
+  constexpr int SZ_SPLIT = (kAuxV + kJaV + (ES && !kEsAllShfl ? 10 : 0)) * n3;   // aux + Ja^r (+ face coupling)
   constexpr int SZ_WEAK = 5 * n3;                                    // F~^r
   constexpr int SZ_V = FORM == 1 ? SZ_SPLIT : SZ_WEAK;
   constexpr int SZ0 = SZ_V > 5 * n3 ? SZ_V : 5 * n3;                 // also holds the new state (Gauss traces)
@@ -735,8 +745,15 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
   // variants at N = 3 and 5 within four waves per SIMD)
   constexpr bool kElemM = FV == 0 || PHYS == 0;
   const NodeMetric nm = node_metric<kElemM>(G, e, n3, t);
+  double ju[AFF ? 10 : 1];
+  if constexpr (AFF) {
+#pragma unroll
+    for (int c = 0; c < 10; ++c) ju[c] = G.em[(size_t)c * nE + e];
+  }
   auto fetch_end = [&]() {
-    if constexpr (kElemM)
+    if constexpr (AFF)
+      sJn = ju[9];
+    else if constexpr (kElemM)
       sJn = nm.sj();
     else
       sJn = G.sJ[(size_t)e * n3 + t];
@@ -758,7 +775,9 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
   auto fetch_dir = [&](int r) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      if constexpr (kElemM)
+      if constexpr (AFF)
+        jn[c] = ju[3 * r + c];
+      else if constexpr (kElemM)
         jn[c] = nm.ja(3 * r + c);
       else
         jn[c] = G.Ja[((size_t)(3 * r + c) * nE + e) * n3 + t];
@@ -825,9 +844,9 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
       const double* Ltr = trace_logs(Utr, nS, n2, TNV);
       const double lg[4] = {Ltr[tr_index(0, 0, 2, nS, side, n2, fi)], Ltr[tr_index(0, 1, 2, nS, side, n2, fi)],
                             Ltr[tr_index(1, 0, 2, nS, side, n2, fi)], Ltr[tr_index(1, 1, 2, nS, side, n2, fi)]};
-      surface_flux_adv<FT, FORM, ROE>(UL, UR, nh, s, P, Phi, &own, slot, lg);
+      surface_flux_adv<FT, FORM, ROE, AFF>(UL, UR, nh, s, P, Phi, &own, slot, lg);
     } else {
-      surface_flux_adv<FT, FORM, ROE>(UL, UR, nh, s, P, Phi);
+      surface_flux_adv<FT, FORM, ROE, AFF>(UL, UR, nh, s, P, Phi);
     }
     if constexpr (ES) {
       double* d = saf + fs * 8 * n2 + rr;
@@ -944,11 +963,12 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
           face_node(f, G.efc[e * 6 + f], ft % n2, kFvf ? f : es_face_slot(f));
         }
       }
-      if (act) {
+      if (!AFF && act) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) sja[c * n3 + t] = jr[c];
       }
-      __syncthreads();
+      // (AFF: nothing of the later directions is staged; ES: the face records are)
+      if (!AFF || ES || r == 0) __syncthreads();
       if (act) {
         if (r < 2) fetch_dir(r + 1);
         else fetch_end();
@@ -960,7 +980,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
         const double c1 = P.c1;
         // two-point flux F#(U_a, ot) . nv
         auto two_point = [&](const Aux& ot, const double nv[3], double F[5]) {
-          if (P.twopoint == 0) {
+          if (AFF || P.twopoint == 0) {
             chandrashekar<FT>(me, ot, nv, c1, F, P.p0, P.ib0);
           } else {
             // central average of the two physical fluxes (states rebuilt from the staged data)
@@ -978,8 +998,9 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
           ot.u[2] = sm[3 * n3 + tl]; ot.beta = sm[4 * n3 + tl]; ot.lrho = sm[5 * n3 + tl];
           ot.lbeta = sm[6 * n3 + tl];
           ot.k = ot.u[0] * ot.u[0] + ot.u[1] * ot.u[1] + ot.u[2] * ot.u[2];
-          const double nv[3] = {0.5 * (jr[0] + sja[0 * n3 + tl]), 0.5 * (jr[1] + sja[1 * n3 + tl]),
-                                0.5 * (jr[2] + sja[2 * n3 + tl])};
+          double nv[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) nv[c] = AFF ? jr[c] : 0.5 * (jr[c] + sja[c * n3 + tl]);
           two_point(ot, nv, F);
         };
         if (kSymLines && (n1 == 4 || r < 2)) {
@@ -1047,7 +1068,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
           // interpolated to the end f of this line; l_f(a) G_f is staged for
           // the line sums S_f = sum_l l_f(l) G_f(l).
           // The surface term of this direction's two faces is applied here too.
-          double* shy = sm + (kAuxV + 3) * n3;
+          double* shy = sm + (kAuxV + kJaV) * n3;
           const int rr = qq * n1 + pp;
 #pragma unroll
           for (int f = 0; f < 2; ++f) {
@@ -1061,7 +1082,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
             for (int l = 0; l < n1; ++l) {
               const int tl = line_node<N>(r, l, pp, qq);
 #pragma unroll
-              for (int c = 0; c < 3; ++c) jf[c] += L[l] * sja[c * n3 + tl];
+              for (int c = 0; c < 3; ++c) jf[c] += L[l] * (AFF ? jr[c] : sja[c * n3 + tl]);
             }
             const double* d = saf + fsl * 8 * n2 + rr;
             Aux of;
@@ -1091,7 +1112,7 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
         // dU_a -= (1/w_a) B_f l_f(a) (G_f(a) - S_f),  B_f = -1 at xi = -1, +1 at xi = +1
         __syncthreads();
         if (act) {
-          const double* shy = sm + (kAuxV + 3) * n3;
+          const double* shy = sm + (kAuxV + kJaV) * n3;
           const int a = idx[r];
           const int pp = r == 0 ? j : i, qq = r == 2 ? j : k;
 #pragma unroll
@@ -1107,7 +1128,8 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
           }
         }
       }
-      __syncthreads();
+      // (AFF, LGL: the tile is read-only from here on; sx has its own barriers)
+      if (!AFF || ES || (MODE == 1 && NODES == 0)) __syncthreads();
     } else {
       // weak form: F~^r = Ja^r . f at every node, then the Dhat contraction
       // (the viscous part comes contracted from the lifting kernel)

@@ -409,16 +409,17 @@ __host__ __device__ inline void roe_dissipation(const double UL[5], const double
 // Phi = [F*(UL,UR).n - lambda_max/2 (UR-UL)] s.
 // ROE selects Roe's dissipation at compile time (its temporaries would raise
 // the register count of every kernel as a run-time branch); otherwise
-// P.riemann chooses Rusanov or no dissipation.  Split form: logs (optional)
+// P.riemann chooses Rusanov or no dissipation; KEP 1 fixes the two-point flux
+// to Chandrashekar's in the same way.  Split form: logs (optional)
 // supplies ln rho, ln beta of UL then UR; with aux the two-point record of UR
 // (side 1) or of UL (side 0) is returned in *aux.
-template <typename FT, int FORM, int ROE = 0>
+template <typename FT, int FORM, int ROE = 0, int KEP = 0>
 __host__ __device__ inline void surface_flux_adv(const double UL[5], const double UR[5], const double nh[3], double s,
                                                  const Phys& P, double Phi[5], Aux* aux = nullptr, int side = 0,
                                                  const double* logs = nullptr) {
   const Prim qL = cons2prim(UL, P.gm1), qR = cons2prim(UR, P.gm1);
   const double nv[3] = {nh[0] * s, nh[1] * s, nh[2] * s};
-  if (FORM == 1 && P.twopoint == 0) {
+  if (FORM == 1 && (KEP || P.twopoint == 0)) {
     const Aux aL = logs ? make_aux_logs(qL, logs[0], logs[1]) : make_aux(qL);
     const Aux aR = logs ? make_aux_logs(qR, logs[2], logs[3]) : make_aux(qR);
     chandrashekar<FT>(aL, aR, nv, P.c1, Phi, P.p0, P.ib0);
