@@ -41,6 +41,7 @@ struct dg_ctx {
   double* d_em = nullptr;               // [10][nE]: constant metric terms per element (Geo::em)
   bool elem_metrics = true;             // kernels take constant elements' terms from d_em
   int n_const_metric = 0;               // elements with constant metric terms in d_em
+  int n_const_side = 0;                 // sides with one normal and surface element (behind d_face)
   double* d_face = nullptr;
   int* d_efc = nullptr;
   DevBasis* d_basis = nullptr;
@@ -421,7 +422,7 @@ static void free_device(dg_ctx* c) {
   for (int** p : {&c->d_etype, &c->d_etype_new, &c->d_sidefv, &c->d_efv, &c->d_side_elem})
     if (*p) { (void)hipFree(*p); *p = nullptr; }
   c->d_Ja = c->d_sJ = c->d_em = c->d_face = nullptr;
-  c->n_const_metric = 0;
+  c->n_const_metric = c->n_const_side = 0;
   c->d_efc = nullptr;
   c->d_basis = nullptr;
   c->mesh_on_device = false;
@@ -693,6 +694,7 @@ static dg_status upload_face(dg_ctx* c, const std::vector<double>& nvec) {
   for (int th = 0; th < nth; ++th) pool.emplace_back(side_block, nS * th / nth, nS * (th + 1) / nth);
   for (auto& th : pool) th.join();
   if (zero) return fail(c, DG_ERR_MESH, "zero face normal");
+  c->n_const_side = (int)std::count(same.begin(), same.end(), 1);
   std::vector<int> efc(c->efc);
   for (int& v : efc)
     if (same[efc_side(v)]) v |= kEfcConst;
@@ -971,7 +973,7 @@ static Cfg kcfg(const dg_ctx* c) {
   k.roe = c->cfg.riemann == DG_RIEMANN_ROE ? 1 : 0;
   k.visc = c->cfg.viscosity == DG_VISC_SUTHERLAND ? 1 : 0;
   k.fv = c->cfg.fv;
-  k.affine = c->n_const_metric == c->nElems;
+  k.affine = c->n_const_metric == c->nElems && c->n_const_side == c->nSides;
   return k;
 }
 

@@ -28,20 +28,22 @@ hipError_t DGX_NAME(launch_trace)(const Cfg& c, const Geo& g, const Phys& p, con
   return hipGetLastError();
 }
 
-template <int NODES>
+template <int NODES, int AFF>
 static void lift_emit(const Cfg& c, int emit, const Geo& g, const Phys& p, const double* U, const double* Utr,
                       double* gout, double* gtr, hipStream_t s) {
   const dim3 grid(g.nElems), block(Shape<kN>::nth);
   if (emit == 0)
-    hipLaunchKernelGGL((k_lift<kN, NODES, 0, 0, 0>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
+    // (gradients on Gauss nodes: bound by their 12 values per node and face node;
+    // the affine variant gained nothing there)
+    hipLaunchKernelGGL((k_lift<kN, NODES, 0, 0, 0, 0, AFF * NODES>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
   else if (c.precision == 0 && c.visc == 0)
-    hipLaunchKernelGGL((k_lift<kN, NODES, 1, 0, 0>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
+    hipLaunchKernelGGL((k_lift<kN, NODES, 1, 0, 0, 0, AFF>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
   else if (c.precision == 0)
-    hipLaunchKernelGGL((k_lift<kN, NODES, 1, 0, 1>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
+    hipLaunchKernelGGL((k_lift<kN, NODES, 1, 0, 1, 0, AFF>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
   else if (c.visc == 0)
-    hipLaunchKernelGGL((k_lift<kN, NODES, 1, 1, 0>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
+    hipLaunchKernelGGL((k_lift<kN, NODES, 1, 1, 0, 0, AFF>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
   else
-    hipLaunchKernelGGL((k_lift<kN, NODES, 1, 1, 1>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
+    hipLaunchKernelGGL((k_lift<kN, NODES, 1, 1, 1, 0, AFF>), grid, block, 0, s, g, p, U, Utr, gout, gtr);
 }
 
 hipError_t DGX_NAME(launch_lift)(const Cfg& c, int emit, const Geo& g, const Phys& p, const double* U,
@@ -66,10 +68,13 @@ hipError_t DGX_NAME(launch_lift)(const Cfg& c, int emit, const Geo& g, const Phy
     hipLaunchKernelGGL((k_lift_fv<kN>), grid, block, 0, s, g, p, U, Utr, gout, gtr2);
     return hipGetLastError();
   }
-  if (c.nodes == 1)
-    lift_emit<1>(c, emit, g, p, U, Utr, gout, gtr, s);
-  else
-    lift_emit<0>(c, emit, g, p, U, Utr, gout, gtr, s);
+  if (c.nodes == 1) {
+    if (c.affine) lift_emit<1, 1>(c, emit, g, p, U, Utr, gout, gtr, s);
+    else lift_emit<1, 0>(c, emit, g, p, U, Utr, gout, gtr, s);
+  } else {
+    if (c.affine) lift_emit<0, 1>(c, emit, g, p, U, Utr, gout, gtr, s);
+    else lift_emit<0, 0>(c, emit, g, p, U, Utr, gout, gtr, s);
+  }
   return hipGetLastError();
 }
 

@@ -99,7 +99,7 @@ struct Cfg {
   int fv;    // FV sub-cells enabled (traces of 10 values, FV kernels)
   int roe;   // Roe's face flux (its own kernel instantiations)
   int visc;  // viscosity law (0 constant, 1 Sutherland; its own lifting instantiations)
-  int affine;  // every element's metric terms are in Geo::em
+  int affine;  // every element's metric terms are in Geo::em, every side's normal behind Geo::face
 };
 
 // Launchers (defined in the kernel translation units).  Each returns the

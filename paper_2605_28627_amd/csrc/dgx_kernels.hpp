@@ -136,6 +136,15 @@ __device__ inline double ld_visc(const double* p, size_t i) {
     return p[i];
 }
 
+// Waves per SIMD the lifting is compiled for (its register budget): on affine
+// meshes an N = 7 LGL element's 50 KB of LDS let three of them share a CU, and
+// its registers fit in 80 without spills (32^3, 2 steps: 21.7 -> 21.2 ms;
+// with 92 registers and two elements per CU the LDS would stay half empty).
+template <int N, int NODES, int EMIT, int AFF>
+constexpr int lift_waves() {
+  return AFF && N == 7 && NODES == 1 && EMIT == 1 ? 6 : 1;
+}
+
 // ---------------------------------------------------------------------------
 // BR1 lifting kernel (paper eq. dgsem_lifted), g = grad (u, v, w, T).
 // EMIT 0: g -> gout[12][nE][n3] and, on Gauss nodes, its face traces ->
@@ -159,21 +168,28 @@ __device__ inline double ld_visc(const double* p, size_t i) {
 // the face-normal viscous flux the element writes the layer-0 sub-cell means
 // of its gradient, B3(J g)/V, to gtr + 8 nSides n2 ([slot][12][side][fi]).
 // ---------------------------------------------------------------------------
-template <int N, int NODES, int EMIT, int PREC, int VL, int FV = 0>
-__global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const double* __restrict__ U,
+//
+// AFF 1 (every element affine, every side with one normal): the metric terms
+// are uniform over the workgroup and live in scalar registers, and the face
+// averages share the LDS of the viscous fluxes, which are formed after them.
+template <int N, int NODES, int EMIT, int PREC, int VL, int FV = 0, int AFF = 0>
+__global__ __launch_bounds__(Shape<N>::nth, (lift_waves<N, NODES, EMIT, AFF>())) void k_lift(Geo G, Phys P, const double* __restrict__ U,
                                                         const double* __restrict__ Utr, double* __restrict__ gout,
                                                         double* __restrict__ gtr) {
   using S = Shape<N>;
   using FT = typename std::conditional<PREC == 1, float, double>::type;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
-  constexpr int SZ = (13 * n3 > 7 * S::nface ? 13 * n3 : 7 * S::nface);
-  constexpr int SZ2 = (12 * n3 > SZ ? 12 * n3 : SZ);
+  // q (4) and the metric rows (9), AFF: q and the face values; then the viscous
+  // fluxes, or on Gauss nodes the gradients (12)
+  constexpr int kHead = AFF ? 4 * n3 + 7 * S::nface : 13 * n3;
+  constexpr int SZ2 = (EMIT == 1 || NODES == 0) && 12 * n3 > kHead ? 12 * n3 : kHead;
   // FV 1, 2: DG elements of an FV context with an FV face (the FV-face code);
   // FV 3: those without one, in the FV context's trace layout only
   constexpr bool kCtx = FV != 0, kFvf = FV == 1 || FV == 2;
   constexpr int TNV = kCtx ? kTrFV : 5;                // trace values per face node
   __shared__ double sm[SZ2];
-  __shared__ double sf[7 * S::nface];
+  __shared__ double sf_own[AFF ? 1 : 7 * S::nface];
+  double* sf = AFF ? sm + 4 * n3 : sf_own;
   // FV contexts: per face node the other (FV) side's sub-face q and the own q;
   // on Gauss nodes the element's state for its own traces
   __shared__ double sfq[kFvf ? 8 * S::nface : 1];
@@ -192,7 +208,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
 #pragma unroll
   for (int it = 0; it < kFI; ++it) finfo[it] = t + it * S::nth < S::nface ? G.efc[e * 6 + face_of<N>(t + it * S::nth)] : 0;
   double* sq = sm;            // [4][n3]
-  double* sja = sm + 4 * n3;  // [9][n3]
+  double* sja = sm + 4 * n3;  // [9][n3] (not AFF)
   const bool act = t < n3;
   const int i = t % n1, j = (t / n1) % n1, k = t / n2;
   double sJ = 0.0;
@@ -252,13 +268,21 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
   double fUL[5], fUR[5], fns[4];
   int fslot = 0;
   const NodeMetric nm = node_metric(G, e, n3, t);
-  const bool elm = G.em[(size_t)9 * nE + e] > 0.0;   // constant metric terms (uniform)
+  const bool elm = AFF || G.em[(size_t)9 * nE + e] > 0.0;   // constant metric terms (uniform)
+  double ju[AFF ? 10 : 1];
+  if constexpr (AFF) {
+#pragma unroll
+    for (int c = 0; c < 10; ++c) ju[c] = G.em[(size_t)c * nE + e];
+    sJ = ju[9];
+  }
   if (act) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) u[v] = U[((size_t)v * nE + e) * n3 + t];
+    if constexpr (!AFF) {
 #pragma unroll
-    for (int c = 0; c < 9; ++c) jl[c] = nm.ja(c);
-    sJ = nm.sj();
+      for (int c = 0; c < 9; ++c) jl[c] = nm.ja(c);
+      sJ = nm.sj();
+    }
   }
   if constexpr (kOneFaceNode && !kFvf) {
     if (t < S::nface) face_load(t, finfo[0], fslot, fUL, fUR, fns);
@@ -278,8 +302,10 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
     sq[1 * n3 + t] = q.u[1];
     sq[2 * n3 + t] = q.u[2];
     sq[3 * n3 + t] = q.p / (q.rho * P.R);
+    if constexpr (!AFF) {
 #pragma unroll
-    for (int c = 0; c < 9; ++c) sja[c * n3 + t] = jl[c];
+      for (int c = 0; c < 9; ++c) sja[c * n3 + t] = jl[c];
+    }
   }
   bc.store(&sb, t);
   // LGL: the face averages read the own q tile (FV contexts: and the own state)
@@ -390,7 +416,8 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
 #pragma unroll
           for (int qa = 0; qa < 4; ++qa) dq[qa] -= c * sq[qa * n3 + tl];
         }
-        const double j0 = sja[(3 * r + 0) * n3 + t], j1 = sja[(3 * r + 1) * n3 + t], j2 = sja[(3 * r + 2) * n3 + t];
+        const double j0 = AFF ? ju[AFF * (3 * r)] : sja[(3 * r + 0) * n3 + t], j1 = AFF ? ju[AFF * (3 * r + 1)] : sja[(3 * r + 1) * n3 + t],
+                     j2 = AFF ? ju[AFF * (3 * r + 2)] : sja[(3 * r + 2) * n3 + t];
 #pragma unroll
         for (int qa = 0; qa < 4; ++qa) {
           acc[3 * qa + 0] += dq[qa] * j0;
@@ -447,7 +474,7 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift(Geo G, Phys P, const dou
     // it), then the Dhat contraction along each node's three lines.
     double jall[9];
 #pragma unroll
-    for (int c = 0; c < 9; ++c) jall[c] = act ? sja[c * n3 + t] : 0.0;
+    for (int c = 0; c < 9; ++c) jall[c] = AFF ? ju[AFF * c] : (act ? sja[c * n3 + t] : 0.0);
     __syncthreads();
     double* sG = sm;   // [4 r + v][n3]
     if (act) {
