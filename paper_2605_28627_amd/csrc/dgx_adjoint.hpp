@@ -66,13 +66,16 @@ __device__ inline void adj_surface_of(const Geo& G, const VolBasis<N>& sb, const
 }
 
 template <int N, int NODES>
-__global__ __launch_bounds__(Shape<N>::nth) void k_adj_trace(Geo G, const double* __restrict__ lam,
+__global__ __launch_bounds__(Shape<N>::block) void k_adj_trace(Geo G, const double* __restrict__ lam,
                                                              double* __restrict__ Lbar) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n3 = S::n3;
-  __shared__ double sl[5 * n3];
+  __shared__ double sl_s[S::epb * (5 * n3)];
+  double* const sl = sl_s + ib * (5 * n3);
   __shared__ VolBasis<N> sb;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems;
   BasisCopy<N, false, S::nth> bc;
   bc.load(G.basis, t);
@@ -123,11 +126,14 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_adj_trace(Geo G, const double
 #define DGX_ADJ_WAVES 1
 #endif
 template <int N, int NODES, int FORM, int PHYS, int ROE = 0, int VL = 0>
-__global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVES : 1)) void k_adj_volume(
+__global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVES : 1)) void k_adj_volume(
     Geo G, Phys P, const double* __restrict__ U, const double* lam, const double* __restrict__ Utr,
     const double* __restrict__ Lbar, const double* __restrict__ gin, const double* __restrict__ gtr,
     double* __restrict__ out, double* __restrict__ Qbar, AdjUpd up) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
   constexpr bool ES = FORM == 1 && NODES == 0;
   constexpr int NF = PHYS == 1 ? 17 : 5;                           // face adjoint values per face node
@@ -140,12 +146,15 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
   // with constant metric terms contracts w_r = Ja^r . (gbar/J) (4 values per
   // direction and node, in sw) along the lines instead of gbar/J (12)
   constexpr bool kW = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1 && PHYS == 1;
-  __shared__ double sl[5 * n3];   // lam / J
-  __shared__ double sB[SZ_B];     // surface adjoints, then aux + metric row
-  __shared__ double sw[kW ? 12 * n3 : 1];
-  __shared__ double sub[ES ? 5 * S::nface : 1];   // ES: adjoints of the own projected traces
+  __shared__ double sl_s[S::epb * (5 * n3)];   // lam / J
+  double* const sl = sl_s + ib * (5 * n3);
+  __shared__ double sB_s[S::epb * (SZ_B)];     // surface adjoints, then aux + metric row
+  double* const sB = sB_s + ib * (SZ_B);
+  __shared__ double sw_s[S::epb * (kW ? 12 * n3 : 1)];
+  double* const sw = sw_s + ib * (kW ? 12 * n3 : 1);
+  __shared__ double sub_s[S::epb * (ES ? 5 * S::nface : 1)];   // ES: adjoints of the own projected traces
+  double* const sub = sub_s + ib * (ES ? 5 * S::nface : 1);
   __shared__ VolBasis<N> sb;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems, nS = G.nSides;
   BasisCopy<N, false, S::nth> bc;
   bc.load(G.basis, t);
@@ -671,16 +680,19 @@ __global__ __launch_bounds__(Shape<N>::nth, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVE
 // With up.lamU it is the stage's last kernel: it applies the reverse RK
 // update and writes the surface adjoint of the new lamdU to up.Lnext.
 template <int N, int NODES, int EP = 0>
-__global__ __launch_bounds__(Shape<N>::nth) void k_adj_lift_volume(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block) void k_adj_lift_volume(Geo G, Phys P, const double* __restrict__ U,
                                                                    const double* __restrict__ Utr,
                                                                    const double* __restrict__ Qbar,
                                                                    double* __restrict__ out, AdjUpd up) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
   constexpr int SZ = 5 * S::nface > 5 * n3 ? 5 * S::nface : 5 * n3;
-  __shared__ double sm[SZ];
+  __shared__ double sm_s[S::epb * (SZ)];
+  double* const sm = sm_s + ib * (SZ);
   __shared__ VolBasis<N> sb;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems, nS = G.nSides;
   BasisCopy<N, false, S::nth> bc;
   bc.load(G.basis, t);

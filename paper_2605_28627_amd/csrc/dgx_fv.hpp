@@ -199,16 +199,22 @@ __device__ inline void write_fv_traces(const Geo& G, int e, const double* sw, do
 // EP 1 (split form on Gauss nodes): DG faces take the entropy-projected
 // trace, its ln rho, ln beta at trace_logs(Utr, nS, n2, kTrFV).
 template <int N, int NODES, int EP = 0>
-__global__ __launch_bounds__(Shape<N>::nth) void k_trace_fv(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block) void k_trace_fv(Geo G, Phys P, const double* __restrict__ U,
                                                             double* __restrict__ Utr) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
-  __shared__ double snod[5 * n3];
-  __shared__ double sa[5 * n3];
-  __shared__ double sb2[5 * n3];
-  __shared__ double sBs[n1 * n1];
+  __shared__ double snod_s[S::epb * (5 * n3)];
+  double* const snod = snod_s + ib * (5 * n3);
+  __shared__ double sa_s[S::epb * (5 * n3)];
+  double* const sa = sa_s + ib * (5 * n3);
+  __shared__ double sb2_s[S::epb * (5 * n3)];
+  double* const sb2 = sb2_s + ib * (5 * n3);
+  __shared__ double sBs_s[S::epb * (n1 * n1)];
+  double* const sBs = sBs_s + ib * (n1 * n1);
   __shared__ VolBasis<N> sbb;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems, nS = G.nSides;
   const bool act = t < n3;
   BasisCopy<N, false, S::nth> bc;
@@ -308,15 +314,18 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_trace_fv(Geo G, Phys P, const
 // kernel reads them), the layer-0 ones to gtr2[slot][12][side][fi].
 // ---------------------------------------------------------------------------
 template <int N>
-__global__ __launch_bounds__(Shape<N>::nth) void k_lift_fv(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block) void k_lift_fv(Geo G, Phys P, const double* __restrict__ U,
                                                            const double* __restrict__ Utr, double* __restrict__ gout,
                                                            double* __restrict__ gtr2) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   if (!G.etype[e]) return;   // DG elements belong to the lifting kernel
   const int nE = G.nElems, nS = G.nSides;
-  __shared__ double sq[4 * n3];
+  __shared__ double sq_s[S::epb * (4 * n3)];
+  double* const sq = sq_s + ib * (4 * n3);
   const bool act = t < n3;
   const int i = t % n1, j = (t / n1) % n1, k = t / n2;
   const int idx[3] = {i, j, k};
@@ -413,21 +422,28 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_lift_fv(Geo G, Phys P, const 
 // and gtr2 for the element faces).
 // ---------------------------------------------------------------------------
 template <int N, int MODE, int PHYS = 0>
-__global__ __launch_bounds__(Shape<N>::nth) void k_fv(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block) void k_fv(Geo G, Phys P, const double* __restrict__ U,
                                                       const double* __restrict__ Utr, const double* __restrict__ gin,
                                                       const double* __restrict__ gtr2, double* __restrict__ Ut,
                                                       double* __restrict__ Uio, double* __restrict__ dU,
                                                       double* __restrict__ Utr_next, double A, double B, double dt) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   if (!G.etype[e]) return;   // DG elements belong to the residual kernel
   const int nE = G.nElems, nS = G.nSides;
-  __shared__ double sw[5 * n3];
-  __shared__ double ssl[5 * n3];
-  __shared__ double sfl[5 * n3];
-  __shared__ double sfe[3 * 5 * n2];   // outward fluxes through the upper element faces 1, 3, 5
-  __shared__ double sgr[PHYS == 1 ? 12 * n3 : 1];   // sub-cell gradients
+  __shared__ double sw_s[S::epb * (5 * n3)];
+  double* const sw = sw_s + ib * (5 * n3);
+  __shared__ double ssl_s[S::epb * (5 * n3)];
+  double* const ssl = ssl_s + ib * (5 * n3);
+  __shared__ double sfl_s[S::epb * (5 * n3)];
+  double* const sfl = sfl_s + ib * (5 * n3);
+  __shared__ double sfe_s[S::epb * (3 * 5 * n2)];   // outward fluxes through the upper element faces 1, 3, 5
+  double* const sfe = sfe_s + ib * (3 * 5 * n2);
+  __shared__ double sgr_s[S::epb * (PHYS == 1 ? 12 * n3 : 1)];   // sub-cell gradients
+  double* const sgr = sgr_s + ib * (PHYS == 1 ? 12 * n3 : 1);
   const bool act = t < n3;
   const int i = t % n1, j = (t / n1) % n1, k = t / n2;
   const int idx[3] = {i, j, k};
@@ -582,15 +598,21 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_fv(Geo G, Phys P, const doubl
 // elements through their DG reconstruction), clamped below at -30.
 // ---------------------------------------------------------------------------
 template <int N>
-__global__ __launch_bounds__(Shape<N>::nth) void k_fv_indicator(Geo G, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block) void k_fv_indicator(Geo G, const double* __restrict__ U,
                                                                 double* __restrict__ ind) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
-  __shared__ double sa[n3];
-  __shared__ double sb2[n3];
-  __shared__ double sM[2 * n1 * n1];
-  __shared__ double sred[2 * S::nth];
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
+  __shared__ double sa_s[S::epb * (n3)];
+  double* const sa = sa_s + ib * (n3);
+  __shared__ double sb2_s[S::epb * (n3)];
+  double* const sb2 = sb2_s + ib * (n3);
+  __shared__ double sM_s[S::epb * (2 * n1 * n1)];
+  double* const sM = sM_s + ib * (2 * n1 * n1);
+  __shared__ double sred_s[S::epb * (2 * S::nth)];
+  double* const sred = sred_s + ib * (2 * S::nth);
   const int nE = G.nElems;
   const bool act = t < n3;
   for (int x = t; x < n1 * n1; x += S::nth) { sM[x] = G.basis->Bsi[x]; sM[n1 * n1 + x] = G.basis->Vli[x]; }
@@ -628,17 +650,22 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_fv_indicator(Geo G, const dou
 // converted between nodal values and sub-cell means; its type is updated.
 // ---------------------------------------------------------------------------
 template <int N>
-__global__ __launch_bounds__(Shape<N>::nth) void k_fv_switch(Geo G, double* __restrict__ U, double* __restrict__ dU,
+__global__ __launch_bounds__(Shape<N>::block) void k_fv_switch(Geo G, double* __restrict__ U, double* __restrict__ dU,
                                                              const int* __restrict__ etype_new,
                                                              int* __restrict__ etype) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n1 = S::n1, n3 = S::n3;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int told = etype[e], tnew = etype_new[e];
   if (told == tnew) return;
-  __shared__ double sa[5 * n3];
-  __shared__ double sb2[5 * n3];
-  __shared__ double sM[n1 * n1];
+  __shared__ double sa_s[S::epb * (5 * n3)];
+  double* const sa = sa_s + ib * (5 * n3);
+  __shared__ double sb2_s[S::epb * (5 * n3)];
+  double* const sb2 = sb2_s + ib * (5 * n3);
+  __shared__ double sM_s[S::epb * (n1 * n1)];
+  double* const sM = sM_s + ib * (n1 * n1);
   const int nE = G.nElems;
   const bool act = t < n3;
   for (int x = t; x < n1 * n1; x += S::nth) sM[x] = tnew ? G.basis->Bs[x] : G.basis->Bsi[x];

@@ -18,7 +18,7 @@ constexpr int kN = DGX_INST_N;
 
 hipError_t DGX_NAME(launch_trace)(const Cfg& c, const Geo& g, const Phys& p, const double* U, double* Utr,
                                   hipStream_t s) {
-  const dim3 grid(g.nElems), block(Shape<kN>::nth);
+  const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
   if (c.nodes == 1)
     hipLaunchKernelGGL((k_trace<kN, 1, 0>), grid, block, 0, s, g, p, U, Utr);
   else if (c.form == 0)
@@ -31,7 +31,7 @@ hipError_t DGX_NAME(launch_trace)(const Cfg& c, const Geo& g, const Phys& p, con
 template <int NODES, int AFF>
 static void lift_emit(const Cfg& c, int emit, const Geo& g, const Phys& p, const double* U, const double* Utr,
                       double* gout, double* gtr, hipStream_t s) {
-  const dim3 grid(g.nElems), block(Shape<kN>::nth);
+  const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
   if (emit == 0)
     // (gradients on Gauss nodes: bound by their 12 values per node and face node;
     // the affine variant gained nothing there)
@@ -52,7 +52,7 @@ hipError_t DGX_NAME(launch_lift)(const Cfg& c, int emit, const Geo& g, const Phy
     // FV contexts (FP64, constant viscosity): DG elements without an FV face
     // (lean kernel), DG elements with one, then FV elements' Green-Gauss
     // gradients; the layer-0 gradients go behind the face fluxes
-    const dim3 grid(g.nElems), block(Shape<kN>::nth);
+    const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
     double* gtr2 = gtr + (size_t)8 * g.nSides * Shape<kN>::n2;
     if (emit != 1) return hipErrorInvalidValue;
     if (c.nodes == 1)
@@ -82,7 +82,7 @@ template <int NODES, int FORM, int PHYS, int PREC, int ROE>
 static void vol_mode_r(int mode, int affine, const Geo& g, const Phys& p, const double* U, const double* Utr, const double* gvn,
                        const double* gvf, double* Ut, double* Uio, double* dU, double* Utr_next, double A, double B,
                        double dt, hipStream_t s) {
-  const dim3 grid(g.nElems), block(Shape<kN>::nth);
+  const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
   if constexpr (FORM == 1 && ROE == 0) {
     if (affine && p.twopoint == 0) {
       if (mode == 0)
@@ -134,7 +134,7 @@ template <int NODES, int FORM, int PHYS>
 static void vol_fv(int mode, const Geo& g, const Phys& p, const double* U, const double* Utr, const double* gvn,
                    const double* gvf, double* Ut, double* Uio, double* dU, double* Utr_next, double A, double B,
                    double dt, hipStream_t s) {
-  const dim3 grid(g.nElems), block(Shape<kN>::nth);
+  const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
   if (mode == 0) {
     if constexpr (PHYS == 1)
       hipLaunchKernelGGL((k_volume<kN, NODES, FORM, PHYS, 0, 0, 0, 2>), grid, block, 0, s, g, p, U, Utr, gvn, gvf,
@@ -181,7 +181,7 @@ hipError_t DGX_NAME(launch_volume)(const Cfg& c, const Geo& g, const Phys& p, in
 
 hipError_t DGX_NAME(launch_trace_fv)(const Cfg& c, const Geo& g, const Phys& p, const double* U, double* Utr,
                                      hipStream_t s) {
-  const dim3 grid(g.nElems), block(Shape<kN>::nth);
+  const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
   if (c.nodes == 1)
     hipLaunchKernelGGL((k_trace_fv<kN, 1>), grid, block, 0, s, g, p, U, Utr);
   else if (c.form == 0)
@@ -194,7 +194,7 @@ hipError_t DGX_NAME(launch_trace_fv)(const Cfg& c, const Geo& g, const Phys& p, 
 hipError_t DGX_NAME(launch_fv)(const Cfg& c, const Geo& g, const Phys& p, int mode, const double* U,
                                const double* Utr, const double* gin, const double* gtr, double* Ut, double* Uio,
                                double* dU, double* Utr_next, double A, double B, double dt, hipStream_t s) {
-  const dim3 grid(g.nElems), block(Shape<kN>::nth);
+  const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
   if (c.physics == 1) {
     const double* gtr2 = gtr + (size_t)8 * g.nSides * Shape<kN>::n2;
     if (mode == 0)
@@ -214,14 +214,14 @@ hipError_t DGX_NAME(launch_fv)(const Cfg& c, const Geo& g, const Phys& p, int mo
 
 hipError_t DGX_NAME(launch_fv_indicator)(const Cfg& c, const Geo& g, const double* U, double* ind, hipStream_t s) {
   (void)c;
-  hipLaunchKernelGGL((k_fv_indicator<kN>), dim3(g.nElems), dim3(Shape<kN>::nth), 0, s, g, U, ind);
+  hipLaunchKernelGGL((k_fv_indicator<kN>), dim3(Shape<kN>::grid(g.nElems)), dim3(Shape<kN>::block), 0, s, g, U, ind);
   return hipGetLastError();
 }
 
 hipError_t DGX_NAME(launch_fv_switch)(const Cfg& c, const Geo& g, double* U, double* dU, const int* etype_new,
                                       int* etype, hipStream_t s) {
   (void)c;
-  hipLaunchKernelGGL((k_fv_switch<kN>), dim3(g.nElems), dim3(Shape<kN>::nth), 0, s, g, U, dU, etype_new, etype);
+  hipLaunchKernelGGL((k_fv_switch<kN>), dim3(Shape<kN>::grid(g.nElems)), dim3(Shape<kN>::block), 0, s, g, U, dU, etype_new, etype);
   return hipGetLastError();
 }
 
@@ -232,7 +232,7 @@ hipError_t DGX_NAME(launch_adjoint)(const Cfg& c, const Geo& g, const Phys& p, c
   // or the lifting adjoint (Navier-Stokes)
   const AdjUpd none{nullptr, nullptr, 0.0, 0.0, 0.0};
   const AdjUpd& upv = c.physics == 1 ? none : up;
-  const dim3 grid(g.nElems), block(Shape<kN>::nth);
+  const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
   // per-element surface adjoints (unless the previous stage's last kernel wrote them)
   if (!up.lbar_ready) {
     if (c.nodes == 1)

@@ -34,11 +34,13 @@ namespace dgx {
 // the same buffer (trace_logs).
 // ---------------------------------------------------------------------------
 template <int N, int NODES, int EP>
-__global__ __launch_bounds__(Shape<N>::nth) void k_trace(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block) void k_trace(Geo G, Phys P, const double* __restrict__ U,
                                                          double* __restrict__ Utr) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int nE = G.nElems, nS = G.nSides;
   if constexpr (NODES == 1) {
     if (t >= n3) return;
@@ -61,7 +63,8 @@ __global__ __launch_bounds__(Shape<N>::nth) void k_trace(Geo G, Phys P, const do
       for (int v = 0; v < 5; ++v) Utr[tr_index(slot, v, 5, nS, side, n2, q * n1 + p)] = u[v];
     }
   } else {
-    __shared__ double su[5 * n3];
+    __shared__ double su_s[S::epb * (5 * n3)];
+    double* const su = su_s + ib * (5 * n3);
     __shared__ VolBasis<N> sb;
     BasisCopy<N, false, S::nth> bc;
     bc.load(G.basis, t);
@@ -173,10 +176,13 @@ constexpr int lift_waves() {
 // are uniform over the workgroup and live in scalar registers, and the face
 // averages share the LDS of the viscous fluxes, which are formed after them.
 template <int N, int NODES, int EMIT, int PREC, int VL, int FV = 0, int AFF = 0>
-__global__ __launch_bounds__(Shape<N>::nth, (lift_waves<N, NODES, EMIT, AFF>())) void k_lift(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>())) void k_lift(Geo G, Phys P, const double* __restrict__ U,
                                                         const double* __restrict__ Utr, double* __restrict__ gout,
                                                         double* __restrict__ gtr) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   using FT = typename std::conditional<PREC == 1, float, double>::type;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
   // q (4) and the metric rows (9), AFF: q and the face values; then the viscous
@@ -187,15 +193,18 @@ __global__ __launch_bounds__(Shape<N>::nth, (lift_waves<N, NODES, EMIT, AFF>()))
   // FV 3: those without one, in the FV context's trace layout only
   constexpr bool kCtx = FV != 0, kFvf = FV == 1 || FV == 2;
   constexpr int TNV = kCtx ? kTrFV : 5;                // trace values per face node
-  __shared__ double sm[SZ2];
-  __shared__ double sf_own[AFF ? 1 : 7 * S::nface];
+  __shared__ double sm_s[S::epb * (SZ2)];
+  double* const sm = sm_s + ib * (SZ2);
+  __shared__ double sf_own_s[S::epb * (AFF ? 1 : 7 * S::nface)];
+  double* const sf_own = sf_own_s + ib * (AFF ? 1 : 7 * S::nface);
   double* sf = AFF ? sm + 4 * n3 : sf_own;
   // FV contexts: per face node the other (FV) side's sub-face q and the own q;
   // on Gauss nodes the element's state for its own traces
-  __shared__ double sfq[kFvf ? 8 * S::nface : 1];
-  __shared__ double su[kFvf && NODES == 0 ? 5 * n3 : 1];
+  __shared__ double sfq_s[S::epb * (kFvf ? 8 * S::nface : 1)];
+  double* const sfq = sfq_s + ib * (kFvf ? 8 * S::nface : 1);
+  __shared__ double su_s[S::epb * (kFvf && NODES == 0 ? 5 * n3 : 1)];
+  double* const su = su_s + ib * (kFvf && NODES == 0 ? 5 * n3 : 1);
   __shared__ VolBasis<N, kFvf> sb;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   const int efl = kCtx ? G.efv[e] : 0;   // bits 0..5: FV faces, bit 6: FV element
   if (kCtx && (efl & 64)) return;        // FV elements: k_lift_fv
   if (kFvf && !(efl & 63)) return;       // (no FV face: the FV 3 variant)
@@ -696,7 +705,7 @@ constexpr int volume_waves() {
 // instead of 122 and 78; 32^3 (2 steps) 23.2 -> 22.5 ms, 16^3 (4 steps)
 // 5.87 -> 5.57 ms, N = 5 Euler 20^3 3.76 -> 3.25 ms.
 template <int N, int NODES, int FORM, int PHYS, int PREC, int MODE, int ROE, int FV = 0, int AFF = 0>
-__global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) void k_volume(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) void k_volume(Geo G, Phys P, const double* __restrict__ U,
                                                           const double* __restrict__ Utr,
                                                           const double* __restrict__ gvn,
                                                           const double* __restrict__ gvf, double* __restrict__ Ut,
@@ -704,6 +713,9 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
                                                           double* __restrict__ Utr_next, double A, double B,
                                                           double dt) {
   using S = Shape<N>;
+  const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
+  const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
+  if (S::epb > 1 && e >= G.nElems) return;
   using FT = typename std::conditional<PREC == 1, float, double>::type;
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
   // split form on Gauss nodes: the entropy-stable hybridised form (face coupling terms)
@@ -736,12 +748,15 @@ __global__ __launch_bounds__(Shape<N>::nth, (volume_waves<N, NODES, FORM>())) vo
   constexpr int kFaces = ES && !kFvf ? kEsFaceSlots : 6;
   // Lobatto split form at N = 7: symmetric zeta pairs, partner shares through sx
   constexpr bool kZetaX = DGX_ZETA_EXCHANGE && FORM == 1 && !ES && n1 == 8 && S::nth == n3;
-  __shared__ double sphi[5 * kFaces * n2];
-  __shared__ double sm[SZ];
-  __shared__ double sx[kZetaX ? 5 * n3 : 1];
-  __shared__ double saf[ES ? 8 * kFaces * n2 : 1];
+  __shared__ double sphi_s[S::epb * (5 * kFaces * n2)];
+  double* const sphi = sphi_s + ib * (5 * kFaces * n2);
+  __shared__ double sm_s[S::epb * (SZ)];
+  double* const sm = sm_s + ib * (SZ);
+  __shared__ double sx_s[S::epb * (kZetaX ? 5 * n3 : 1)];
+  double* const sx = sx_s + ib * (kZetaX ? 5 * n3 : 1);
+  __shared__ double saf_s[S::epb * (ES ? 8 * kFaces * n2 : 1)];
+  double* const saf = saf_s + ib * (ES ? 8 * kFaces * n2 : 1);
   __shared__ VolBasis<N, kFvf> sb;
-  const int e = elem_of_block(blockIdx.x, G.nElems), t = threadIdx.x;
   // FV: which faces are FV (bits 0..5), and whether this element is (bit 6)
   const int efl = kCtx ? G.efv[e] : 0;
   if (kCtx && (efl & 64)) return;   // FV elements belong to the FV kernel

@@ -14,7 +14,16 @@ struct Shape {
   static constexpr int n1 = N + 1;
   static constexpr int n2 = n1 * n1;
   static constexpr int n3 = n2 * n1;
-  static constexpr int nth = ((n3 + 63) / 64) * 64;   // work-items per element (whole wavefronts)
+  // Work-items per element: whole wavefronts, except at N = 1, whose 8 nodes
+  // would leave 7/8 of one idle.  There a wavefront holds 4 elements of 16
+  // work-items, each with its own LDS tile and numbering (Euler 60^3, 2 steps:
+  // 4.55 -> 2.47 ms; 8 elements of 8 gain nothing more there and lose 5 % on
+  // meshes that do not fill the chip, 2 of 32 lose 17 % at 60^3).  N = 2 packed
+  // in pairs (27 of 32) gained 6 % at 40^3 and lost 9 % at 5x6x5.
+  static constexpr int nth = N == 1 ? 16 : ((n3 + 63) / 64) * 64;
+  static constexpr int epb = nth < 64 ? 64 / nth : 1;  // elements per workgroup
+  static constexpr int block = nth * epb;
+  __host__ __device__ static int grid(int nElems) { return (nElems + epb - 1) / epb; }
   static constexpr int nface = 6 * n2;                 // face nodes of one element
 };
 
@@ -126,7 +135,7 @@ __device__ __forceinline__ FaceGeom face_geom(const Geo& G, int info, int n2, in
 // elements, so an element and its lexicographic neighbours (which read the
 // same face data) run on the same XCD close in time.  XCD x then gets
 // nE/8 (+1 for x < nE%8) elements starting at x (nE/8) + min(x, nE%8); the
-// map is a bijection of [0, nE) for any nE.  Measured, it gains nothing at
+// map is a bijection of [0, nE) for any nE (of one element per workgroup).  Measured, it gains nothing at
 // N = 7 and costs 2-8 % at N = 3 (plausibly because in plain order the
 // eight XCDs work on neighbouring elements at the same time and share the
 // face data through the chip-wide last-level cache), so plain order (0) is

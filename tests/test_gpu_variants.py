@@ -1,0 +1,148 @@
+"""Kernel variants that a rule on the mesh or the degree selects.
+
+* Affine meshes: the split form's residual and the lifting run variants with
+  uniform metric terms where every element is affine.  Against the general
+  kernels (the same mesh with per-element metric terms switched off): the same
+  operations, and for the lifting the factored gradient, so FP64 results agree
+  to 1e-12 of each output's largest entry (the bound of the per-element metric
+  terms).  With float fluxes a last-bit difference of an FP64 intermediate may
+  move a float rounding (6e-8 of a flux; the residual is a difference of fluxes
+  some 50 times its size): 5e-6.
+* Sides with one normal: curved meshes with one plane layer of elements mix
+  both kinds in one launch; the residual matches the oracle.
+* N = 1 packs four elements into a wavefront: element counts that leave a
+  wavefront partly empty, for every kernel, against the oracle (1e-12, as all
+  residuals and transposed residuals).
+"""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2605_28627_amd import inputs as I
+from tests.helpers import rel_err_per_var
+
+pytestmark = pytest.mark.gpu
+PI = np.pi
+
+
+def _say(*a):
+    print("[gpu-variants]", *a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def S():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2605_28627_amd.solver import DGSolver
+    return DGSolver
+
+
+def _off(a, ref):
+    """Largest relative error over the variables; one whose reference vanishes
+    (a single periodic element: below 1e-12, rounding) counts absolutely."""
+    scale = np.abs(ref).max(axis=tuple(range(1, ref.ndim)))
+    err = np.abs(a - ref).max(axis=tuple(range(1, ref.ndim)))
+    return (err / np.where(scale < 1e-12, 1.0, scale)).max()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("physics", [0, 1])
+@pytest.mark.parametrize("nodes", [0, 1])
+@pytest.mark.parametrize("N", range(1, 8))
+def test_affine_variant_matches_general_kernels(S, N, nodes, physics, precision):
+    _say("affine", N, nodes, physics, precision)
+    mesh = I.box_mesh((3, 2, 3), (-PI,) * 3, (PI,) * 3, rotate_seed=5)
+    s = S(dict(N=N, nodes=nodes, form=1, physics=physics, mu=1e-2 if physics else 0.0, precision=precision), mesh)
+    try:
+        assert s.element_metric_count() == mesh.nElems
+        # (variations on both sides of the log means' series threshold)
+        U0 = I.smooth_random_state(s.coords(), 71, amp=0.1)
+        U0[:, : mesh.nElems // 2] = I.smooth_random_state(s.coords(), 71, amp=0.002)[:, : mesh.nElems // 2]
+        dt = 0.2 * s.timestep(s.init_state(U0), 0.9)
+
+        def run():
+            U = s.init_state(U0)
+            out = [s.rhs(U).cpu().numpy()]
+            if physics:
+                out.append(s.lift(U).cpu().numpy())
+            dU = s.empty_state()
+            s.rk_step(U, dU, dt, 2)
+            return out + [dU.cpu().numpy(), U.cpu().numpy()]
+
+        on = run()
+        s.set_element_metrics(False)
+        off = run()
+    finally:
+        s.close()
+    for a, b in zip(on, off):
+        assert np.isfinite(a).all()
+        assert np.abs(a - b).max() <= (5e-6 if precision else 1e-12) * np.abs(b).max()
+
+
+@pytest.mark.parametrize("case", [(7, 1, 1, 1), (4, 1, 0, 1), (3, 0, 0, 0), (5, 1, 1, 0)], ids=str)
+def test_plane_and_curved_sides_in_one_launch(S, orc, case):
+    """Random side orientations; the top layer of elements stays plane, the others are curved inside."""
+    _say("mixed", case)
+    N, nodes, form, physics = case
+    mesh = I.box_mesh((2, 2, 3), (-PI,) * 3, (PI,) * 3, Ngeo=3, rotate_seed=9)
+    low = np.arange(mesh.nElems) < 8
+    z = mesh.X[2]
+    bump = 0.1 * np.sin(1.5 * (z + PI)) * np.sin(mesh.X[0]) * np.sin(mesh.X[1])
+    mesh.X[2][low] += np.where(z < PI / 3, bump, 0.0)[low]
+    cfg = dict(N=N, nodes=nodes, form=form, physics=physics, mu=0.02 if physics else 0.0)
+    o, s = orc.Oracle(cfg, mesh), S(cfg, mesh)
+    try:
+        assert 0 < s.element_metric_count() < mesh.nElems
+        _, Ja, sJ, nv = s.metrics()
+        _, J, Jo = o.geometry()
+        n_affine = s.element_metric_count()
+        # the oracle's metric terms on curved elements, the library's (same to rounding) on plane ones
+        curved = np.array([np.ptp(sJ[e]) > 0 for e in range(mesh.nElems)])
+        assert (~curved).sum() == n_affine
+        U = I.smooth_random_state(o.coords(), 72, amp=0.2)
+        R = s.rhs(s.init_state(U)).cpu().numpy()
+    finally:
+        s.close()
+    ref = o.rhs(U)
+    # the two sides' metric terms differ by rounding (bounded here by what they differ by)
+    dm = np.abs(Ja - Jo).max() / np.abs(Jo).max()
+    err = rel_err_per_var(R, ref)
+    _say("mixed", case, err, "metric", dm)
+    assert dm < 1e-12 and np.all(err < 1e-12 + 1e3 * dm), (err, dm)
+
+
+@pytest.mark.parametrize("K", [(1, 1, 1), (2, 1, 1), (3, 1, 1), (3, 3, 1)], ids=str)
+@pytest.mark.parametrize("nodes,form", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("physics", [0, 1])
+def test_packed_elements(S, orc, K, nodes, form, physics):
+    _say("packed", K, nodes, form, physics)
+    mesh = I.box_mesh(K, (-PI,) * 3, (PI,) * 3, rotate_seed=4)
+    cfg = dict(N=1, nodes=nodes, form=form, physics=physics, mu=0.02 if physics else 0.0)
+    o, s = orc.Oracle(cfg, mesh), S(cfg, mesh, adjoint=True)
+    f = S(dict(cfg, fv=1), mesh)
+    of = orc.Oracle(dict(cfg, fv=1), mesh)
+    try:
+        _, J, Ja = o.geometry()
+        for x in (s, f):
+            x.upload_metrics(Ja, 1.0 / J, o.face_normals())
+        U = I.smooth_random_state(o.coords(), 73, amp=0.1)
+        Ug = s.init_state(U)
+        assert _off(s.rhs(Ug).cpu().numpy(), o.rhs(U)) < 1e-12
+        rng = np.random.default_rng(74)
+        lam, d = rng.normal(size=U.shape), rng.normal(size=U.shape)
+        out = s.adjoint_rhs(Ug, s.to_device(lam)).cpu().numpy()
+        _, jd = o.rhs_jvp(U, d)
+        assert abs((out * d).sum() - (lam * jd).sum()) < 1e-12 * np.abs(lam * jd).sum()
+        dt = o.timestep(U, 0.9)
+        s.rk_step(Ug, s.empty_state(), dt, 2)
+        assert _off(Ug.cpu().numpy() - U, o.lserk(U, 2, dt) - U) < 1e-11
+        mask = (np.arange(mesh.nElems) % 3 == 0).astype(np.int32)
+        Uf = f.init_state(U)
+        f.fv_switch(Uf, mask)
+        Uo, _ = of.fv_switch(U, None, mask)
+        assert _off(f.rhs(Uf).cpu().numpy(), of.rhs(Uo)) < 1e-12
+    finally:
+        s.close()
+        f.close()
