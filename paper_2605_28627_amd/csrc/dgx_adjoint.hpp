@@ -119,14 +119,22 @@ __global__ __launch_bounds__(Shape<N>::block) void k_adj_trace(Geo G, const doub
 // W = sum_l w_l, so each node reverses its own G_f and the u~_f parts are
 // summed along the line.  Phase 4 maps them back through the projection:
 // (du/dv)^T at each face node, l_f along the lines, (dv/dU)^T at each node.
-// Waves per SIMD requested for 512-work-item adjoint kernels: 1 leaves the
-// register file to one element per CU (the Jacobian chain stays in registers),
-// 4 would cap it at 128 VGPRs for two elements per CU and spill.
-#ifndef DGX_ADJ_WAVES
-#define DGX_ADJ_WAVES 1
-#endif
-template <int N, int NODES, int FORM, int PHYS, int ROE = 0, int VL = 0>
-__global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WAVES : 1)) void k_adj_volume(
+// Waves per SIMD requested for 512-work-item adjoint kernels.  The affine
+// variant on LGL nodes fits two elements per CU: 74 KB of LDS (no staged
+// w_r, no metric rows) and 128 VGPRs with 28 B of spills (Euler: none); one
+// element per CU left the SIMDs two waves each, 43 % busy (16^3 reverse step
+// 4.61 -> 3.95 ms, Euler 12^3 1.21 -> 0.93 ms).  The others hold 170-256
+// registers: at 128 they spill hundreds of bytes, so they keep one.
+template <int N, int NODES, int AFF>
+constexpr int adj_waves() {
+  return Shape<N>::nth >= 512 ? (AFF && NODES == 1 ? 4 : 1) : 1;
+}
+//
+// AFF 1 (split form, every element affine, Chandrashekar's flux): uniform
+// metric terms in scalar registers, no metric rows in LDS, the central flux
+// compiled out (as k_volume).
+template <int N, int NODES, int FORM, int PHYS, int ROE = 0, int VL = 0, int AFF = 0>
+__global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void k_adj_volume(
     Geo G, Phys P, const double* __restrict__ U, const double* lam, const double* __restrict__ Utr,
     const double* __restrict__ Lbar, const double* __restrict__ gin, const double* __restrict__ gtr,
     double* __restrict__ out, double* __restrict__ Qbar, AdjUpd up) {
@@ -139,13 +147,14 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
   constexpr int NF = PHYS == 1 ? 17 : 5;                           // face adjoint values per face node
   constexpr int SZ_F = NF * S::nface;
   // aux (8) + one metric row (3) (+ ES: the coupling's u~_f parts of both faces, 10)
-  constexpr int SZ_V = FORM == 1 ? (ES ? 21 : 11) * n3 : 0;
+  constexpr int kJaV = AFF ? 0 : 3;
+  constexpr int SZ_V = FORM == 1 ? ((ES ? 18 : 8) + kJaV) * n3 : 0;
   constexpr int SZ_B = SZ_F > SZ_V ? SZ_F : SZ_V;
   constexpr bool kSymLines = DGX_SYMMETRIC_PAIRS && (n1 == 4 || n1 == 8) && (n3 % 64 == 0);
   // N = 7 LGL split form, Navier-Stokes: the lifting adjoint of an element
   // with constant metric terms contracts w_r = Ja^r . (gbar/J) (4 values per
   // direction and node, in sw) along the lines instead of gbar/J (12)
-  constexpr bool kW = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1 && PHYS == 1;
+  constexpr bool kW = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1 && PHYS == 1 && !AFF;
   __shared__ double sl_s[S::epb * (5 * n3)];   // lam / J
   double* const sl = sl_s + ib * (5 * n3);
   __shared__ double sB_s[S::epb * (SZ_B)];     // surface adjoints, then aux + metric row
@@ -162,7 +171,12 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
   const int i = t % n1, j = (t / n1) % n1, k = t / n2;
   const int idx[3] = {i, j, k};
   const NodeMetric nm = node_metric(G, e, n3, t);
-  const double sJ = act ? nm.sj() : 0.0;
+  double ju[AFF ? 10 : 1];
+  if constexpr (AFF) {
+#pragma unroll
+    for (int c = 0; c < 10; ++c) ju[c] = G.em[(size_t)c * nE + e];
+  }
+  const double sJ = AFF ? ju[AFF * 9] : (act ? nm.sj() : 0.0);
   if (act) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) sl[v * n3 + t] = sJ * lam[((size_t)v * nE + e) * n3 + t];
@@ -172,7 +186,7 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
   // (N = 7) the registers hold them from the start, so that their latency
   // overlaps the surface phase; elsewhere each is (re)loaded where it is
   // used, which keeps the other kernels' occupancy and spill-free budgets.
-  constexpr bool kPrefetch = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1;
+  constexpr bool kPrefetch = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1 && !AFF;
   const bool elm = kW && G.em[(size_t)9 * nE + e] > 0.0;   // constant metric terms (uniform)
   double un[5] = {0, 0, 0, 0, 0}, jn[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   double gn[PHYS == 1 ? 12 : 1];
@@ -184,7 +198,7 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
   };
   auto load_row = [&](int r) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) jn[3 * r + c] = nm.ja(3 * r + c);
+    for (int c = 0; c < 3; ++c) jn[3 * r + c] = AFF ? ju[AFF * (3 * r + c)] : nm.ja(3 * r + c);
   };
   auto load_g = [&]() {
     if constexpr (PHYS == 1) {
@@ -476,12 +490,12 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
       if (act) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          if (!kPrefetch) jn[3 * r + c] = nm.ja(3 * r + c);
+          if (!kPrefetch) jn[3 * r + c] = AFF ? ju[AFF * (3 * r + c)] : nm.ja(3 * r + c);
           jr[c] = jn[3 * r + c];
-          sja[c * n3 + t] = jr[c];
+          if (!AFF) sja[c * n3 + t] = jr[c];
         }
       }
-      __syncthreads();
+      if (!AFF || r == 0) __syncthreads();
       if (act) {
         const int a = idx[r];
         const int pp = r == 0 ? j : i, qq = r == 2 ? j : k;
@@ -490,9 +504,9 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
           ot.u[2] = saux[3 * n3 + tl]; ot.beta = saux[4 * n3 + tl]; ot.lrho = saux[5 * n3 + tl];
           ot.lbeta = saux[6 * n3 + tl]; ot.k = saux[7 * n3 + tl];
 #pragma unroll
-          for (int c = 0; c < 3; ++c) nv[c] = 0.5 * (jr[c] + sja[c * n3 + tl]);
+          for (int c = 0; c < 3; ++c) nv[c] = AFF ? jr[c] : 0.5 * (jr[c] + sja[c * n3 + tl]);
         };
-        if (P.twopoint == 0 && kSymLines && (n1 == 4 || r < 2)) {
+        if ((AFF || P.twopoint == 0) && kSymLines && (n1 == 4 || r < 2)) {
           const int lane = t & 63;
           const int str = r == 0 ? 1 : (r == 1 ? n1 : n2);
 #pragma unroll 1
@@ -530,7 +544,7 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
             double w[5];
 #pragma unroll
             for (int v = 0; v < 5; ++v) w[v] = -(dml * lm[v] + dlm * sl[v * n3 + tl]);
-            if (P.twopoint == 0) {
+            if (AFF || P.twopoint == 0) {
               AuxBar d;
               chandrashekar_vjp_a(me, ot, nv, c1, w, d);
               ab.rho += d.rho; ab.u[0] += d.u[0]; ab.u[1] += d.u[1]; ab.u[2] += d.u[2];
@@ -550,7 +564,7 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
         if constexpr (ES) {
           // face coupling of this direction's two faces: node a reverses its
           // G_f(a) with the weight w_a - l_f(a) W; the u~_f parts go to sred
-          double* sred = sB + 11 * n3;   // [2 faces][5][n3]
+          double* sred = sB + (8 + kJaV) * n3;   // [2 faces][5][n3]
 #pragma unroll
           for (int f = 0; f < 2; ++f) {
             const double* L = f ? sb.Lp : sb.Lm;
@@ -569,7 +583,7 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
               const int tl = line_node<N>(r, l, pp, qq);
               const double cw = sg * sb.winv[l] * L[l];
 #pragma unroll
-              for (int c = 0; c < 3; ++c) jf[c] += L[l] * sja[c * n3 + tl];
+              for (int c = 0; c < 3; ++c) jf[c] += L[l] * (AFF ? jr[c] : sja[c * n3 + tl]);
 #pragma unroll
               for (int v = 0; v < 5; ++v) W[v] += cw * sl[v * n3 + tl];
             }
@@ -578,7 +592,7 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
             double om[5], Uf[5];
 #pragma unroll
             for (int v = 0; v < 5; ++v) om[v] = ca * lm[v] - L[a] * W[v];
-            if (P.twopoint == 0) {
+            if (AFF || P.twopoint == 0) {
               const Aux af = make_aux(qf);
               AuxBar da, dfb;
               chandrashekar_vjp_ab(me, af, nv, c1, om, da, dfb);
@@ -600,10 +614,10 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
           }
         }
       }
-      __syncthreads();
+      if (!AFF || ES) __syncthreads();
       if constexpr (ES) {
         // the u~_f parts of this direction's faces, summed along each line
-        const double* sred = sB + 11 * n3;
+        const double* sred = sB + (8 + kJaV) * n3;
         for (int ft = t; ft < 2 * n2; ft += S::nth) {
           const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1;
 #pragma unroll
@@ -616,7 +630,7 @@ __global__ __launch_bounds__(Shape<N>::block, (Shape<N>::nth >= 512 ? DGX_ADJ_WA
         }
       }
     }
-    if (act && P.twopoint == 0) {
+    if (act && (AFF || P.twopoint == 0)) {
       if (!kPrefetch) load_u();
       const double* u = un;
       const Prim q = cons2prim(u, P.gm1);

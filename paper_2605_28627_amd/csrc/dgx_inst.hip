@@ -242,8 +242,14 @@ hipError_t DGX_NAME(launch_adjoint)(const Cfg& c, const Geo& g, const Phys& p, c
   }
   // volume + surface adjoint
 #define DGX_ADJ_V(NODES, FORM, PHYS, ROE, VL)                                                                  \
-  hipLaunchKernelGGL((k_adj_volume<kN, NODES, FORM, PHYS, ROE, VL>), grid, block, 0, s, g, p, U, lam, Utr, Lbar, gin, \
-                     gtr, out, qbar, upv)
+  do {                                                                                                         \
+    if (FORM == 1 && ROE == 0 && VL == 0 && c.affine && p.twopoint == 0)                                       \
+      hipLaunchKernelGGL((k_adj_volume<kN, NODES, FORM, PHYS, ROE, VL, FORM * (1 - ROE) * (1 - VL)>), grid, block, 0, s, g, \
+                         p, U, lam, Utr, Lbar, gin, gtr, out, qbar, upv);                                      \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_adj_volume<kN, NODES, FORM, PHYS, ROE, VL>), grid, block, 0, s, g, p, U, lam, Utr, \
+                         Lbar, gin, gtr, out, qbar, upv);                                                      \
+  } while (0)
   // (Sutherland's law only matters with viscous terms)
 #define DGX_ADJ(NODES, FORM, PHYS)                                       \
   do {                                                                   \
