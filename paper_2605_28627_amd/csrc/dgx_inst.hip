@@ -84,13 +84,15 @@ static void vol_mode_r(int mode, int affine, const Geo& g, const Phys& p, const 
                        double dt, hipStream_t s) {
   const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
   if constexpr (FORM == 1 && ROE == 0) {
-    if (affine && p.twopoint == 0) {
-      if (mode == 0)
-        hipLaunchKernelGGL((k_volume<kN, NODES, FORM, PHYS, PREC, 0, ROE, 0, 1>), grid, block, 0, s, g, p, U, Utr, gvn,
-                           gvf, Ut, Uio, dU, Utr_next, A, B, dt);
-      else
-        hipLaunchKernelGGL((k_volume<kN, NODES, FORM, PHYS, PREC, 1, ROE, 0, 1>), grid, block, 0, s, g, p, U, Utr, gvn,
-                           gvf, Ut, Uio, dU, Utr_next, A, B, dt);
+    if (p.twopoint == 0) {
+#define DGX_VOL_VAR(MODE, VAR)                                                                                         \
+  hipLaunchKernelGGL((k_volume<kN, NODES, FORM, PHYS, PREC, MODE, ROE, 0, VAR>), grid, block, 0, s, g, p, U, Utr, gvn, \
+                     gvf, Ut, Uio, dU, Utr_next, A, B, dt)
+      if (affine && mode == 0) DGX_VOL_VAR(0, 1);
+      else if (affine) DGX_VOL_VAR(1, 1);
+      else if (mode == 0) DGX_VOL_VAR(0, 2);
+      else DGX_VOL_VAR(1, 2);
+#undef DGX_VOL_VAR
       return;
     }
   }

@@ -682,7 +682,7 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
 // element's LDS small enough for three waves per SIMD at N=3.
 __host__ __device__ constexpr int es_face_slot(int f) { return f < 4 ? f : f - 4; }
 constexpr int kEsFaceSlots = 4;
-template <int N, int NODES, int FORM>
+template <int N, int NODES, int FORM, int VAR = 0>
 constexpr int volume_waves() {
   return Shape<N>::nth >= 512 ? 4 : ((FORM == 1 && NODES == 0 && N == 3) ? DGX_ES_WAVES : 1);
 }
@@ -696,7 +696,7 @@ constexpr int volume_waves() {
 // both layer-0 sub-cells' viscous fluxes, from the gradients at
 // gvf + 8 nSides n2.
 //
-// AFF 1 (split form, every element of the mesh affine, Chandrashekar's flux):
+// VAR 1 (split form, every element of the mesh affine, Chandrashekar's flux):
 // the metric terms are uniform over the workgroup and live in scalar
 // registers; no metric rows in LDS (N = 7: 12 KB), none read per pair, and no
 // barriers between directions whose pairs stay inside a wavefront.  The
@@ -704,14 +704,18 @@ constexpr int volume_waves() {
 // registers as a run-time choice.  N = 7 Navier-Stokes: 105 VGPRs and 66 KB
 // instead of 122 and 78; 32^3 (2 steps) 23.2 -> 22.5 ms, 16^3 (4 steps)
 // 5.87 -> 5.57 ms, N = 5 Euler 20^3 3.76 -> 3.25 ms.
-template <int N, int NODES, int FORM, int PHYS, int PREC, int MODE, int ROE, int FV = 0, int AFF = 0>
-__global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) void k_volume(Geo G, Phys P, const double* __restrict__ U,
+// VAR 2: the central flux compiled out, metric terms from the node arrays (any
+// mesh; curved N = 5: 111 instead of 138 VGPRs, four waves per SIMD instead of
+// three, 24^3 (2 steps) 5.50 -> 5.23 ms).  VAR 0: either two-point flux, Roe.
+template <int N, int NODES, int FORM, int PHYS, int PREC, int MODE, int ROE, int FV = 0, int VAR = 0>
+__global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM, VAR>())) void k_volume(Geo G, Phys P, const double* __restrict__ U,
                                                           const double* __restrict__ Utr,
                                                           const double* __restrict__ gvn,
                                                           const double* __restrict__ gvf, double* __restrict__ Ut,
                                                           double* __restrict__ Uio, double* __restrict__ dU,
                                                           double* __restrict__ Utr_next, double A, double B,
                                                           double dt) {
+  constexpr int kAff = VAR == 1, kKep = VAR >= 1;
   using S = Shape<N>;
   const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
   const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
@@ -728,7 +732,7 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
   constexpr bool kEsAllShfl = kSymLines && n1 == 4;
   // the two-point record of every node (7 values; |u|^2 is recomputed from u)
   constexpr int kAuxV = 7;
-  constexpr int kJaV = AFF ? 0 : 3;
+  constexpr int kJaV = kAff ? 0 : 3;
   constexpr int SZ_SPLIT = (kAuxV + kJaV + (ES && !kEsAllShfl ? 10 : 0)) * n3;   // aux + Ja^r (+ face coupling)
   constexpr int SZ_WEAK = 5 * n3;                                    // F~^r
   constexpr int SZ_V = FORM == 1 ? SZ_SPLIT : SZ_WEAK;
@@ -748,12 +752,19 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
   constexpr int kFaces = ES && !kFvf ? kEsFaceSlots : 6;
   // Lobatto split form at N = 7: symmetric zeta pairs, partner shares through sx
   constexpr bool kZetaX = DGX_ZETA_EXCHANGE && FORM == 1 && !ES && n1 == 8 && S::nth == n3;
+  // Lobatto split form at N = 4, 5, 6, whose lines straddle wavefronts in
+  // every direction: symmetric pairs with the shares through sx in all three
+  // (N = 5: 9 instead of 15 pairs per node; 20^3 Euler, 4 steps: 3.28 -> 2.82
+  // ms.  N = 2 would go from 2 pairs to 1 and a round trip through LDS: no
+  // gain).  The work-items beyond the
+  // element's nodes repeat its last node, for the barriers' sake.
+  constexpr bool kExch = DGX_ZETA_EXCHANGE && FORM == 1 && !ES && !kSymLines && n1 > 3;
   __shared__ double sphi_s[S::epb * (5 * kFaces * n2)];
   double* const sphi = sphi_s + ib * (5 * kFaces * n2);
   __shared__ double sm_s[S::epb * (SZ)];
   double* const sm = sm_s + ib * (SZ);
-  __shared__ double sx_s[S::epb * (kZetaX ? 5 * n3 : 1)];
-  double* const sx = sx_s + ib * (kZetaX ? 5 * n3 : 1);
+  __shared__ double sx_s[S::epb * (kZetaX || kExch ? 5 * n3 : 1)];
+  double* const sx = sx_s + ib * (kZetaX || kExch ? 5 * n3 : 1);
   __shared__ double saf_s[S::epb * (ES ? 8 * kFaces * n2 : 1)];
   double* const saf = saf_s + ib * (ES ? 8 * kFaces * n2 : 1);
   __shared__ VolBasis<N, kFvf> sb;
@@ -770,7 +781,8 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
 #pragma unroll
   for (int it = 0; it < kFI; ++it) finfo[it] = t + it * S::nth < S::nface ? G.efc[e * 6 + face_of<N>(t + it * S::nth)] : 0;
   const bool act = t < n3;
-  const int i = t % n1, j = (t / n1) % n1, k = t / n2;
+  const int tt = kExch && t >= n3 ? n3 - 1 : t;
+  const int i = tt % n1, j = (tt / n1) % n1, k = tt / n2;
   const int idx[3] = {i, j, k};
   // Loads of the own state and of direction 0's metric row (and G~^0) are
   // issued first, so that their latency overlaps the surface fluxes; each
@@ -787,13 +799,13 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
   // variants at N = 3 and 5 within four waves per SIMD)
   constexpr bool kElemM = FV == 0 || PHYS == 0;
   const NodeMetric nm = node_metric<kElemM>(G, e, n3, t);
-  double ju[AFF ? 10 : 1];
-  if constexpr (AFF) {
+  double ju[kAff ? 10 : 1];
+  if constexpr (kAff) {
 #pragma unroll
     for (int c = 0; c < 10; ++c) ju[c] = G.em[(size_t)c * nE + e];
   }
   auto fetch_end = [&]() {
-    if constexpr (AFF)
+    if constexpr (kAff)
       sJn = ju[9];
     else if constexpr (kElemM)
       sJn = nm.sj();
@@ -817,7 +829,7 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
   auto fetch_dir = [&](int r) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      if constexpr (AFF)
+      if constexpr (kAff)
         jn[c] = ju[3 * r + c];
       else if constexpr (kElemM)
         jn[c] = nm.ja(3 * r + c);
@@ -886,9 +898,9 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
       const double* Ltr = trace_logs(Utr, nS, n2, TNV);
       const double lg[4] = {Ltr[tr_index(0, 0, 2, nS, side, n2, fi)], Ltr[tr_index(0, 1, 2, nS, side, n2, fi)],
                             Ltr[tr_index(1, 0, 2, nS, side, n2, fi)], Ltr[tr_index(1, 1, 2, nS, side, n2, fi)]};
-      surface_flux_adv<FT, FORM, ROE, AFF>(UL, UR, nh, s, P, Phi, &own, slot, lg);
+      surface_flux_adv<FT, FORM, ROE, kKep>(UL, UR, nh, s, P, Phi, &own, slot, lg);
     } else {
-      surface_flux_adv<FT, FORM, ROE, AFF>(UL, UR, nh, s, P, Phi);
+      surface_flux_adv<FT, FORM, ROE, kKep>(UL, UR, nh, s, P, Phi);
     }
     if constexpr (ES) {
       double* d = saf + fs * 8 * n2 + rr;
@@ -1005,24 +1017,24 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
           face_node(f, G.efc[e * 6 + f], ft % n2, kFvf ? f : es_face_slot(f));
         }
       }
-      if (!AFF && act) {
+      if (!kAff && act) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) sja[c * n3 + t] = jr[c];
       }
-      // (AFF: nothing of the later directions is staged; ES: the face records are)
-      if (!AFF || ES || r == 0) __syncthreads();
+      // (kAff: nothing of the later directions is staged; ES: the face records are)
+      if (!kAff || ES || r == 0) __syncthreads();
       if (act) {
         if (r < 2) fetch_dir(r + 1);
         else fetch_end();
       }
       double Gf[2][5];   // face coupling of this node (ES)
-      if (act) {
+      if (act || kExch) {
         const int a = idx[r];
         const int pp = r == 0 ? j : i, qq = r == 2 ? j : k;
         const double c1 = P.c1;
         // two-point flux F#(U_a, ot) . nv
         auto two_point = [&](const Aux& ot, const double nv[3], double F[5]) {
-          if (AFF || P.twopoint == 0) {
+          if (kKep || P.twopoint == 0) {
             chandrashekar<FT>(me, ot, nv, c1, F, P.p0, P.ib0);
           } else {
             // central average of the two physical fluxes (states rebuilt from the staged data)
@@ -1042,7 +1054,7 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
           ot.k = ot.u[0] * ot.u[0] + ot.u[1] * ot.u[1] + ot.u[2] * ot.u[2];
           double nv[3];
 #pragma unroll
-          for (int c = 0; c < 3; ++c) nv[c] = AFF ? jr[c] : 0.5 * (jr[c] + sja[c * n3 + tl]);
+          for (int c = 0; c < 3; ++c) nv[c] = kAff ? jr[c] : 0.5 * (jr[c] + sja[c * n3 + tl]);
           two_point(ot, nv, F);
         };
         if (kSymLines && (n1 == 4 || r < 2)) {
@@ -1069,27 +1081,28 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
               for (int v = 0; v < 5; ++v) acc[v] += __shfl(-dba * F[v], src);
             }
           }
-        } else if (kZetaX && r == 2) {
-          // The zeta line crosses the element's waves: the pair (a, a+d) is
+        } else if (kExch || (kZetaX && r == 2)) {
+          // The line crosses the element's waves: the pair (a, a+d) is
           // evaluated once, by the node of a, which hands -DS[a+d][a] F to
-          // the node of a+d through sx (every node of the block takes part:
-          // the element fills it).  Distance n1/2 is met from both ends.
+          // the node of a+d through sx.  Distance n1/2 is met from both ends.
 #pragma unroll 1
           for (int d = 1; d <= n1 / 2; ++d) {
-            const int b = (a + d) & (n1 - 1);
+            const int b = a + d < n1 ? a + d : a + d - n1;
             const int tb = line_node<N>(r, b, pp, qq);
             double F[5];
             pair_flux(tb, F);
             const double dab = sb.DS[a * n1 + b];
 #pragma unroll
             for (int v = 0; v < 5; ++v) acc[v] -= dab * F[v];
-            if (d < n1 / 2) {
+            if (2 * d < n1) {
               const double dba = sb.DS[b * n1 + a];
+              if (act) {
 #pragma unroll
-              for (int v = 0; v < 5; ++v) sx[v * n3 + tb] = -dba * F[v];
+                for (int v = 0; v < 5; ++v) sx[v * n3 + tb] = -dba * F[v];
+              }
               __syncthreads();
 #pragma unroll
-              for (int v = 0; v < 5; ++v) acc[v] += sx[v * n3 + t];
+              for (int v = 0; v < 5; ++v) acc[v] += sx[v * n3 + tt];
               __syncthreads();
             }
           }
@@ -1124,7 +1137,7 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
             for (int l = 0; l < n1; ++l) {
               const int tl = line_node<N>(r, l, pp, qq);
 #pragma unroll
-              for (int c = 0; c < 3; ++c) jf[c] += L[l] * (AFF ? jr[c] : sja[c * n3 + tl]);
+              for (int c = 0; c < 3; ++c) jf[c] += L[l] * (kAff ? jr[c] : sja[c * n3 + tl]);
             }
             const double* d = saf + fsl * 8 * n2 + rr;
             Aux of;
@@ -1170,8 +1183,8 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) 
           }
         }
       }
-      // (AFF, LGL: the tile is read-only from here on; sx has its own barriers)
-      if (!AFF || ES || (MODE == 1 && NODES == 0)) __syncthreads();
+      // (kAff, LGL: the tile is read-only from here on; sx has its own barriers)
+      if (!kAff || ES || (MODE == 1 && NODES == 0)) __syncthreads();
     } else {
       // weak form: F~^r = Ja^r . f at every node, then the Dhat contraction
       // (the viscous part comes contracted from the lifting kernel)
