@@ -3,7 +3,7 @@
 // Same layout as the forward kernels (one workgroup per element, one
 // work-item per node, element data in LDS).  With lt = lam / J:
 //   surface:  each element writes t = -(1/w) l(+-1) lt along its normal lines
-//             (k_adj_trace); the side flux's adjoint is t_master - t_slave;
+//             (k_adj_begin); the side flux's adjoint is t_master - t_slave;
 //   volume:   weak form  F~^r_l gets sum_a Dhat[a][l] lt_a (transposed
 //             contraction along the line); split form: node m gets
 //             -sum_l J_A(m,l)^T (DS[m][l] lt_m + DS[l][m] lt_l), J_A the
@@ -65,27 +65,81 @@ __device__ inline void adj_surface_of(const Geo& G, const VolBasis<N>& sb, const
   }
 }
 
-template <int N, int NODES>
-__global__ __launch_bounds__(Shape<N>::block) void k_adj_trace(Geo G, const double* __restrict__ lam,
+// Start of an adjoint stage, one pass over the element's nodes: the traces of
+// the state U (EP as in k_trace), lam = scale * src (stored in lam_out unless
+// null: the step's first stage starts with lamdU = B lamU), and the surface
+// adjoint of lam.  As kernels of their own the three took 5 us each on meshes
+// too small to fill the chip, of 45 us for an Euler stage (8^3, N = 5).
+template <int N, int NODES, int EP>
+__global__ __launch_bounds__(Shape<N>::block) void k_adj_begin(Geo G, Phys P, const double* __restrict__ U,
+                                                             double* __restrict__ Utr, const double* __restrict__ src,
+                                                             double scale, double* __restrict__ lam_out,
                                                              double* __restrict__ Lbar) {
   using S = Shape<N>;
   const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
   const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
   if (S::epb > 1 && e >= G.nElems) return;
-  constexpr int n3 = S::n3;
+  constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
   __shared__ double sl_s[S::epb * (5 * n3)];
   double* const sl = sl_s + ib * (5 * n3);
+  __shared__ double su_s[S::epb * (5 * n3)];
+  double* const su = su_s + ib * (5 * n3);
   __shared__ VolBasis<N> sb;
-  const int nE = G.nElems;
+  const int nE = G.nElems, nS = G.nSides;
   BasisCopy<N, false, S::nth> bc;
   bc.load(G.basis, t);
   if (t < n3) {
-    const double sJ = node_metric(G, e, n3, t).sj();
+    double u[5], l[5];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sl[v * n3 + t] = sJ * lam[((size_t)v * nE + e) * n3 + t];
+    for (int v = 0; v < 5; ++v) {
+      const size_t gi = ((size_t)v * nE + e) * n3 + t;
+      u[v] = U[gi];
+      l[v] = src[gi];
+    }
+    const double sJ = node_metric(G, e, n3, t).sj();
+    if constexpr (EP == 1) {
+      double w[5];
+      entropy_vars(cons2prim(u, P.gm1), P.gm1, w);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) u[v] = w[v];
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      su[v * n3 + t] = u[v];
+      l[v] *= scale;
+      if (lam_out) lam_out[((size_t)v * nE + e) * n3 + t] = l[v];
+      sl[v * n3 + t] = sJ * l[v];
+    }
   }
   bc.store(&sb, t);
   __syncthreads();
+  for (int ft = t; ft < S::nface; ft += S::nth) {
+    const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
+    const int info = G.efc[e * 6 + f];
+    const int side = efc_side(info), slot = efc_slot(info);
+    int p = pp, q = qq;
+    if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, q);
+    double acc[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      if constexpr (NODES == 1) {
+        acc[v] = su[v * n3 + line_node<N>(r, (f & 1) ? N : 0, pp, qq)];
+      } else {
+        const double* L = (f & 1) ? sb.Lp : sb.Lm;
+        acc[v] = 0.0;
+#pragma unroll
+        for (int a = 0; a < n1; ++a) acc[v] += L[a] * su[v * n3 + line_node<N>(r, a, pp, qq)];
+      }
+    }
+    if constexpr (EP == 1) {
+      double w[5], lg[2];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) w[v] = acc[v];
+      entropy_to_cons(w, P.gm1, acc, lg);   // (the adjoint reads no trace logarithms)
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) Utr[tr_index(slot, v, 5, nS, side, n2, q * n1 + p)] = acc[v];
+  }
   adj_surface_of<N, NODES>(G, sb, sl, e, t, Lbar);
 }
 

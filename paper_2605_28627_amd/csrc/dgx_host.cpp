@@ -1072,11 +1072,7 @@ dg_status dg_rk_step(dg_ctx* c, double* U, double* dU, double t, double dt, int 
   double A[DG_RK_MAX_STAGES], B[DG_RK_MAX_STAGES];
   const int ns = rk_scheme(c, A, B);
   Work w = kwork(c);
-  const size_t n = (size_t)5 * c->nElems * c->n3;
-  {
-    ProfScope ps(c, FAM_OTHER, s);
-    LAUNCHCHK(c, launch_fill(dU, n, 0.0, s));
-  }
+  // (dU needs no clearing: the schemes' first stage has A = 0 and does not read it)
   st = traces(c, U, w.Utr[0], s);
   if (st != DG_OK) return st;
   int cur = 0;
@@ -1102,10 +1098,6 @@ dg_status dg_rk_step_stages(dg_ctx* c, double* U, double* dU, double t, double d
   const int ns = rk_scheme(c, A, B);
   Work w = kwork(c);
   const size_t n = (size_t)5 * c->nElems * c->n3;
-  {
-    ProfScope ps(c, FAM_OTHER, s);
-    LAUNCHCHK(c, launch_fill(dU, n, 0.0, s));
-  }
   st = traces(c, U, w.Utr[0], s);
   if (st != DG_OK) return st;
   // stage k reads its input (U, then Y_k) and writes the next stage's input
@@ -1160,8 +1152,11 @@ static dg_status ready_adjoint(dg_ctx* c, const char* who) {
   return DG_OK;
 }
 
-// out = (dR/dU(U))^T lam, with the forward traces (and gradients) of U recomputed.
-static dg_status adjoint_residual(dg_ctx* c, const double* U, const double* lam, double* out, hipStream_t s,
+// out = (dR/dU(U))^T lam, with the forward traces (and gradients) of U
+// recomputed.  begin: also lam's surface adjoint (else the previous stage wrote
+// it), with lam = scale src first where src is given.
+static dg_status adjoint_residual(dg_ctx* c, const double* U, double* lam, double* out, hipStream_t s, bool begin,
+                                  const double* src = nullptr, double scale = 1.0,
                                   const AdjUpd& up = AdjUpd{nullptr, nullptr, 0.0, 0.0, 0.0}) {
   Cfg k = kcfg(c);
   Geo g = kgeo(c);
@@ -1170,7 +1165,10 @@ static dg_status adjoint_residual(dg_ctx* c, const double* U, const double* lam,
   double* qbar = k.physics == DG_PHYS_NAVIER_STOKES ? (double*)(c->ws + L.qbar) : nullptr;
   {
     ProfScope ps(c, FAM_TRACE, s);
-    LAUNCHCHK(c, launch_trace(k, g, c->phys, U, w.Utr[0], s));
+    if (begin)
+      LAUNCHCHK(c, launch_adj_begin(k, g, c->phys, U, w.Utr[0], src ? src : lam, scale, src ? lam : nullptr, w.Utr[1], s));
+    else
+      LAUNCHCHK(c, launch_trace(k, g, c->phys, U, w.Utr[0], s));
   }
   if (k.physics == DG_PHYS_NAVIER_STOKES) {
     ProfScope ps(c, FAM_LIFT, s);
@@ -1186,7 +1184,7 @@ dg_status dg_adjoint_rhs(dg_ctx* c, const double* U, const double* lam, double* 
   if (st != DG_OK) return st;
   if (!U || !lam || !out) return fail(c, DG_ERR_ARG, "dg_adjoint_rhs: null pointer");
   if (out == U || out == lam) return fail(c, DG_ERR_ARG, "dg_adjoint_rhs: out aliases an input");
-  return adjoint_residual(c, U, lam, out, (hipStream_t)stream);
+  return adjoint_residual(c, U, const_cast<double*>(lam), out, (hipStream_t)stream, true);   // (lam is only read)
 }
 
 // Reverse sweep of one RK step over the stage inputs Y[0..S-1]:
@@ -1195,12 +1193,7 @@ static dg_status reverse_sweep(dg_ctx* c, const double* const* Y, double* lamU, 
                                hipStream_t s) {
   double A[DG_RK_MAX_STAGES], B[DG_RK_MAX_STAGES];
   const int ns = rk_scheme(c, A, B);
-  const size_t n = (size_t)5 * c->nElems * c->n3;
   double* aout = (double*)(c->ws + ws_layout(c).aout);
-  {
-    ProfScope ps(c, FAM_OTHER, s);
-    LAUNCHCHK(c, launch_scale_copy(n, lamU, lamdU, B[ns - 1], s));
-  }
   // (the update is fused into the stage's last adjoint kernel, which for
   // Navier-Stokes also writes the next stage's surface adjoint into Lbar:
   // nothing else touches that buffer before the next stage reads it)
@@ -1209,8 +1202,9 @@ static dg_status reverse_sweep(dg_ctx* c, const double* const* Y, double* lamU, 
   for (int k = ns - 1; k >= 0; --k) {
     AdjUpd up{lamU, lamdU, dt, A[k], k > 0 ? B[k - 1] : 0.0};
     up.Lnext = visc && k > 0 ? Lbar : nullptr;
-    up.lbar_ready = visc && k < ns - 1 ? 1 : 0;
-    dg_status st = adjoint_residual(c, Y[k], lamdU, aout, s, up);
+    const bool first = k == ns - 1;
+    dg_status st = adjoint_residual(c, Y[k], lamdU, aout, s, first || !visc, first ? lamU : nullptr,
+                                    first ? B[ns - 1] : 1.0, up);
     if (st != DG_OK) return st;
   }
   return DG_OK;
@@ -1236,16 +1230,11 @@ dg_status dg_adjoint_rk_step(dg_ctx* c, const double* Un, double* lamU, double* 
   const int ns = rk_scheme(c, A, B);
   WsLayout L = ws_layout(c);
   Work w = kwork(c);
-  const size_t n = (size_t)5 * c->nElems * c->n3;
   const double* Y[DG_RK_MAX_STAGES];
   Y[0] = Un;
   for (int k = 0; k + 1 < ns; ++k) Y[k + 1] = (const double*)(c->ws + L.Y[k]);
   double* dUf = (double*)(c->ws + L.dUf);
   // recompute the stage inputs Y_1..Y_{S-1} of this step
-  {
-    ProfScope ps(c, FAM_OTHER, s);
-    LAUNCHCHK(c, launch_fill(dUf, n, 0.0, s));
-  }
   {
     ProfScope ps(c, FAM_TRACE, s);
     LAUNCHCHK(c, launch_trace(kcfg(c), kgeo(c), c->phys, Un, w.Utr[0], s));

@@ -227,6 +227,18 @@ hipError_t DGX_NAME(launch_fv_switch)(const Cfg& c, const Geo& g, double* U, dou
   return hipGetLastError();
 }
 
+hipError_t DGX_NAME(launch_adj_begin)(const Cfg& c, const Geo& g, const Phys& p, const double* U, double* Utr,
+                                      const double* src, double scale, double* lam_out, double* Lbar, hipStream_t s) {
+  const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
+  if (c.nodes == 1)
+    hipLaunchKernelGGL((k_adj_begin<kN, 1, 0>), grid, block, 0, s, g, p, U, Utr, src, scale, lam_out, Lbar);
+  else if (c.form == 0)
+    hipLaunchKernelGGL((k_adj_begin<kN, 0, 0>), grid, block, 0, s, g, p, U, Utr, src, scale, lam_out, Lbar);
+  else
+    hipLaunchKernelGGL((k_adj_begin<kN, 0, 1>), grid, block, 0, s, g, p, U, Utr, src, scale, lam_out, Lbar);
+  return hipGetLastError();
+}
+
 hipError_t DGX_NAME(launch_adjoint)(const Cfg& c, const Geo& g, const Phys& p, const double* U, const double* lam,
                                     const double* Utr, double* Lbar, const double* gin, const double* gtr,
                                     double* out, double* qbar, const AdjUpd& up, hipStream_t s) {
@@ -235,13 +247,6 @@ hipError_t DGX_NAME(launch_adjoint)(const Cfg& c, const Geo& g, const Phys& p, c
   const AdjUpd none{nullptr, nullptr, 0.0, 0.0, 0.0};
   const AdjUpd& upv = c.physics == 1 ? none : up;
   const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
-  // per-element surface adjoints (unless the previous stage's last kernel wrote them)
-  if (!up.lbar_ready) {
-    if (c.nodes == 1)
-      hipLaunchKernelGGL((k_adj_trace<kN, 1>), grid, block, 0, s, g, lam, Lbar);
-    else
-      hipLaunchKernelGGL((k_adj_trace<kN, 0>), grid, block, 0, s, g, lam, Lbar);
-  }
   // volume + surface adjoint
 #define DGX_ADJ_V(NODES, FORM, PHYS, ROE, VL)                                                                  \
   do {                                                                                                         \

@@ -126,11 +126,8 @@ struct AdjUpd {
   double* lamdU;
   double dt, A, Bnext;
   // Navier-Stokes: the surface adjoint of the updated lamdU (the next stage's
-  // lam) is written to Lnext by the same kernel (null: not wanted); with
-  // lbar_ready the Lbar of this stage's lam was written that way and the
-  // surface-adjoint kernel is skipped
+  // lam) is written to Lnext by the same kernel (null: not wanted)
   double* Lnext;
-  int lbar_ready;
 };
 
 // out = (dR/dU)^T lam (or, with up.lamU, the fused update); Utr holds the
@@ -138,6 +135,8 @@ struct AdjUpd {
 // forward lifted gradients and their traces, qbar [2][4][nSides][n2] takes
 // the lifting adjoint's face values, and out is scratch too when the update
 // is fused).
+// (Lbar, the surface adjoint of lam, written by launch_adj_begin or by the
+// previous stage's last kernel.)
 hipError_t launch_adjoint(const Cfg& c, const Geo& g, const Phys& p, const double* U, const double* lam,
                           const double* Utr, double* Lbar, const double* gin, const double* gtr, double* out,
                           double* qbar, const AdjUpd& up, hipStream_t s);
@@ -160,8 +159,10 @@ hipError_t launch_fv_decide(int nElems, const double* ind, double lo, double hi,
                             hipStream_t s);
 hipError_t launch_fv_side_flags(int nSides, const int* side_elem, const int* etype, int* sidefv, hipStream_t s);
 hipError_t launch_fv_elem_flags(int nElems, const int* efc, const int* sidefv, const int* etype, int* efv, hipStream_t s);
-hipError_t launch_scale_copy(size_t n, const double* x, double* y, double a, hipStream_t s);
-hipError_t launch_fill(double* x, size_t n, double v, hipStream_t s);
+// Start of an adjoint stage: traces of U, lam = scale src (stored in lam_out
+// unless null) and its surface adjoint Lbar.
+hipError_t launch_adj_begin(const Cfg& c, const Geo& g, const Phys& p, const double* U, double* Utr, const double* src,
+                            double scale, double* lam_out, double* Lbar, hipStream_t s);
 hipError_t launch_fill_int(int* x, size_t n, int v, hipStream_t s);
 hipError_t launch_kinetic_energy(const Cfg& c, const Geo& g, const double* U, double* partial, double* out,
                                  double scale, hipStream_t s);

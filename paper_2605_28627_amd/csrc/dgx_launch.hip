@@ -50,6 +50,8 @@ hipError_t static_scratch(void** ptr) {
   hipError_t launch_adjoint_N##n(const Cfg&, const Geo&, const Phys&, const double*, const double*,          \
                                  const double*, double*, const double*, const double*, double*, double*,       \
                                  const AdjUpd&, hipStream_t);                                                   \
+  hipError_t launch_adj_begin_N##n(const Cfg&, const Geo&, const Phys&, const double*, double*, const double*, \
+                                   double, double*, double*, hipStream_t);                                     \
   hipError_t launch_trace_fv_N##n(const Cfg&, const Geo&, const Phys&, const double*, double*, hipStream_t);   \
   hipError_t launch_fv_N##n(const Cfg&, const Geo&, const Phys&, int, const double*, const double*,         \
                             const double*, const double*, double*, double*, double*, double*, double, double,  \
@@ -168,6 +170,13 @@ hipError_t launch_volume(const Cfg& c, const Geo& g, const Phys& p, int mode, co
 #undef ARGS
 }
 
+hipError_t launch_adj_begin(const Cfg& c, const Geo& g, const Phys& p, const double* U, double* Utr, const double* src,
+                            double scale, double* lam_out, double* Lbar, hipStream_t s) {
+#define ARGS (c, g, p, U, Utr, src, scale, lam_out, Lbar, s)
+  DGX_SWITCH(launch_adj_begin)
+#undef ARGS
+}
+
 hipError_t launch_adjoint(const Cfg& c, const Geo& g, const Phys& p, const double* U, const double* lam,
                           const double* Utr, double* Lbar, const double* gin, const double* gtr, double* out,
                           double* qbar, const AdjUpd& up, hipStream_t s) {
@@ -183,37 +192,10 @@ constexpr int kRedBlocks = 1024;
 constexpr int kRedThreads = 256;
 int reduction_blocks() { return kRedBlocks; }
 
-__global__ void k_fill(double* x, size_t n, double v) {
-  for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x) x[t] = v;
-}
 __global__ void k_fill_int(int* x, size_t n, int v) {
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x) x[t] = v;
 }
 
-// y = a x (the reverse LSERK sweep starts with lamdU = B_{S-1} lamU).
-__global__ void k_scale_copy(size_t n, const double* __restrict__ x, double* __restrict__ y, double a) {
-  for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x)
-    y[t] = a * x[t];
-}
-
-static unsigned grid_for(size_t n) {
-  size_t nb = (n + 255) / 256;
-  if (nb > 65536) nb = 65536;
-  return (unsigned)(nb ? nb : 1);
-}
-
-hipError_t launch_scale_copy(size_t n, const double* x, double* y, double a, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_copy, dim3(grid_for(n)), dim3(256), 0, s, n, x, y, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill(double* x, size_t n, double v, hipStream_t s) {
-  size_t nb = (n + 255) / 256;
-  if (nb > 65536) nb = 65536;
-  if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill, dim3((unsigned)nb), dim3(256), 0, s, x, n, v);
-  return hipGetLastError();
-}
 hipError_t launch_fill_int(int* x, size_t n, int v, hipStream_t s) {
   size_t nb = (n + 255) / 256;
   if (nb > 65536) nb = 65536;
