@@ -179,19 +179,21 @@ __global__ __launch_bounds__(Shape<N>::block) void k_adj_begin(Geo G, Phys P, co
 // element per CU left the SIMDs two waves each, 43 % busy (16^3 reverse step
 // 4.61 -> 3.95 ms, Euler 12^3 1.21 -> 0.93 ms).  The others hold 170-256
 // registers: at 128 they spill hundreds of bytes, so they keep one.
-template <int N, int NODES, int AFF>
+template <int N, int NODES, int VAR>
 constexpr int adj_waves() {
-  return Shape<N>::nth >= 512 ? (AFF && NODES == 1 ? 4 : 1) : 1;
+  return Shape<N>::nth >= 512 ? (VAR == 1 && NODES == 1 ? 4 : 1) : 1;
 }
 //
-// AFF 1 (split form, every element affine, Chandrashekar's flux): uniform
+// VAR 1 (split form, every element affine, Chandrashekar's flux): uniform
 // metric terms in scalar registers, no metric rows in LDS, the central flux
-// compiled out (as k_volume).
-template <int N, int NODES, int FORM, int PHYS, int ROE = 0, int VL = 0, int AFF = 0>
-__global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void k_adj_volume(
+// compiled out (as k_volume).  VAR 2: the central flux compiled out, metric
+// terms from the node arrays.
+template <int N, int NODES, int FORM, int PHYS, int ROE = 0, int VL = 0, int VAR = 0>
+__global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, VAR>())) void k_adj_volume(
     Geo G, Phys P, const double* __restrict__ U, const double* lam, const double* __restrict__ Utr,
     const double* __restrict__ Lbar, const double* __restrict__ gin, const double* __restrict__ gtr,
     double* __restrict__ out, double* __restrict__ Qbar, AdjUpd up) {
+  constexpr int kAff = VAR == 1, kKep = VAR >= 1;
   using S = Shape<N>;
   const int ib = S::epb == 1 ? 0 : (int)threadIdx.x / S::nth, t = (int)threadIdx.x - ib * S::nth;
   const int e = elem_of_block(blockIdx.x, S::grid(G.nElems)) * S::epb + ib;
@@ -201,14 +203,19 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
   constexpr int NF = PHYS == 1 ? 17 : 5;                           // face adjoint values per face node
   constexpr int SZ_F = NF * S::nface;
   // aux (8) + one metric row (3) (+ ES: the coupling's u~_f parts of both faces, 10)
-  constexpr int kJaV = AFF ? 0 : 3;
-  constexpr int SZ_V = FORM == 1 ? ((ES ? 18 : 8) + kJaV) * n3 : 0;
+  constexpr int kJaV = kAff ? 0 : 3;
+  // lines that straddle wavefronts: each pair once, the partner's share (6
+  // values) through LDS behind the aux data (as k_volume; N = 7: the zeta lines)
+  constexpr bool kPairs = (n1 == 4 || n1 == 8) && n3 % 64 == 0;
+  constexpr bool kExch = kKep && FORM == 1 && !ES && !kPairs && n1 > 3;
+  constexpr bool kZetaX = kAff && FORM == 1 && !ES && n1 == 8;
+  constexpr int SZ_V = FORM == 1 ? ((ES ? 18 : 8) + kJaV + (kExch || kZetaX ? 6 : 0)) * n3 : 0;
   constexpr int SZ_B = SZ_F > SZ_V ? SZ_F : SZ_V;
   constexpr bool kSymLines = DGX_SYMMETRIC_PAIRS && (n1 == 4 || n1 == 8) && (n3 % 64 == 0);
   // N = 7 LGL split form, Navier-Stokes: the lifting adjoint of an element
   // with constant metric terms contracts w_r = Ja^r . (gbar/J) (4 values per
   // direction and node, in sw) along the lines instead of gbar/J (12)
-  constexpr bool kW = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1 && PHYS == 1 && !AFF;
+  constexpr bool kW = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1 && PHYS == 1 && !kAff;
   __shared__ double sl_s[S::epb * (5 * n3)];   // lam / J
   double* const sl = sl_s + ib * (5 * n3);
   __shared__ double sB_s[S::epb * (SZ_B)];     // surface adjoints, then aux + metric row
@@ -222,15 +229,16 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
   BasisCopy<N, false, S::nth> bc;
   bc.load(G.basis, t);
   const bool act = t < n3;
-  const int i = t % n1, j = (t / n1) % n1, k = t / n2;
+  const int tt = kExch && t >= n3 ? n3 - 1 : t;   // (work-items beyond the nodes repeat the last one)
+  const int i = tt % n1, j = (tt / n1) % n1, k = tt / n2;
   const int idx[3] = {i, j, k};
   const NodeMetric nm = node_metric(G, e, n3, t);
-  double ju[AFF ? 10 : 1];
-  if constexpr (AFF) {
+  double ju[kAff ? 10 : 1];
+  if constexpr (kAff) {
 #pragma unroll
     for (int c = 0; c < 10; ++c) ju[c] = G.em[(size_t)c * nE + e];
   }
-  const double sJ = AFF ? ju[AFF * 9] : (act ? nm.sj() : 0.0);
+  const double sJ = kAff ? ju[kAff * 9] : (act ? nm.sj() : 0.0);
   if (act) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) sl[v * n3 + t] = sJ * lam[((size_t)v * nE + e) * n3 + t];
@@ -240,7 +248,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
   // (N = 7) the registers hold them from the start, so that their latency
   // overlaps the surface phase; elsewhere each is (re)loaded where it is
   // used, which keeps the other kernels' occupancy and spill-free budgets.
-  constexpr bool kPrefetch = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1 && !AFF;
+  constexpr bool kPrefetch = S::nth >= 512 && ROE == 0 && NODES == 1 && FORM == 1 && !kAff;
   const bool elm = kW && G.em[(size_t)9 * nE + e] > 0.0;   // constant metric terms (uniform)
   double un[5] = {0, 0, 0, 0, 0}, jn[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   double gn[PHYS == 1 ? 12 : 1];
@@ -252,7 +260,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
   };
   auto load_row = [&](int r) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) jn[3 * r + c] = AFF ? ju[AFF * (3 * r + c)] : nm.ja(3 * r + c);
+    for (int c = 0; c < 3; ++c) jn[3 * r + c] = kAff ? ju[kAff * (3 * r + c)] : nm.ja(3 * r + c);
   };
   auto load_g = [&]() {
     if constexpr (PHYS == 1) {
@@ -544,13 +552,13 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
       if (act) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          if (!kPrefetch) jn[3 * r + c] = AFF ? ju[AFF * (3 * r + c)] : nm.ja(3 * r + c);
+          if (!kPrefetch) jn[3 * r + c] = kAff ? ju[kAff * (3 * r + c)] : nm.ja(3 * r + c);
           jr[c] = jn[3 * r + c];
-          if (!AFF) sja[c * n3 + t] = jr[c];
+          if (!kAff) sja[c * n3 + t] = jr[c];
         }
       }
-      if (!AFF || r == 0) __syncthreads();
-      if (act) {
+      if (!kAff || r == 0) __syncthreads();
+      if (act || kExch) {
         const int a = idx[r];
         const int pp = r == 0 ? j : i, qq = r == 2 ? j : k;
         auto partner = [&](int tl, Aux& ot, double nv[3]) {
@@ -558,9 +566,9 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
           ot.u[2] = saux[3 * n3 + tl]; ot.beta = saux[4 * n3 + tl]; ot.lrho = saux[5 * n3 + tl];
           ot.lbeta = saux[6 * n3 + tl]; ot.k = saux[7 * n3 + tl];
 #pragma unroll
-          for (int c = 0; c < 3; ++c) nv[c] = AFF ? jr[c] : 0.5 * (jr[c] + sja[c * n3 + tl]);
+          for (int c = 0; c < 3; ++c) nv[c] = kAff ? jr[c] : 0.5 * (jr[c] + sja[c * n3 + tl]);
         };
-        if ((AFF || P.twopoint == 0) && kSymLines && (n1 == 4 || r < 2)) {
+        if ((kKep || P.twopoint == 0) && kSymLines && (n1 == 4 || r < 2)) {
           const int lane = t & 63;
           const int str = r == 0 ? 1 : (r == 1 ? n1 : n2);
 #pragma unroll 1
@@ -586,6 +594,37 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
               ab.lbeta += __shfl(db.lbeta, src); ab.k += __shfl(db.k, src);
             }
           }
+        } else if (kExch || (kZetaX && r == 2)) {
+          double* sxc = sB + (8 + kJaV) * n3;   // [6][n3]
+#pragma unroll 1
+          for (int d = 1; d <= n1 / 2; ++d) {
+            const int b = a + d < n1 ? a + d : a + d - n1;
+            const int tl = line_node<N>(r, b, pp, qq);
+            Aux ot;
+            double nv[3];
+            partner(tl, ot, nv);
+            const double dab = sb.DS[a * n1 + b], dba = sb.DS[b * n1 + a];
+            double w[5];
+#pragma unroll
+            for (int v = 0; v < 5; ++v) w[v] = -(dab * lm[v] + dba * sl[v * n3 + tl]);
+            AuxBar da, db;
+            chandrashekar_vjp_ab(me, ot, nv, c1, w, da, db);
+            ab.rho += da.rho; ab.u[0] += da.u[0]; ab.u[1] += da.u[1]; ab.u[2] += da.u[2];
+            ab.beta += da.beta; ab.lrho += da.lrho; ab.lbeta += da.lbeta; ab.k += da.k;
+            if (2 * d < n1) {
+              // (the logarithms' adjoints, zero in the series branch, go as rho's and beta's)
+              if (db.lrho != 0.0) db.rho += db.lrho * rcp_nr(ot.rho);
+              if (db.lbeta != 0.0) db.beta += db.lbeta * rcp_nr(ot.beta);
+              if (act) {
+                sxc[tl] = db.rho; sxc[n3 + tl] = db.u[0]; sxc[2 * n3 + tl] = db.u[1]; sxc[3 * n3 + tl] = db.u[2];
+                sxc[4 * n3 + tl] = db.beta; sxc[5 * n3 + tl] = db.k;
+              }
+              __syncthreads();
+              ab.rho += sxc[tt]; ab.u[0] += sxc[n3 + tt]; ab.u[1] += sxc[2 * n3 + tt]; ab.u[2] += sxc[3 * n3 + tt];
+              ab.beta += sxc[4 * n3 + tt]; ab.k += sxc[5 * n3 + tt];
+              __syncthreads();
+            }
+          }
         } else {
 #pragma unroll 1
           for (int l = 0; l < n1; ++l) {
@@ -598,7 +637,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
             double w[5];
 #pragma unroll
             for (int v = 0; v < 5; ++v) w[v] = -(dml * lm[v] + dlm * sl[v * n3 + tl]);
-            if (AFF || P.twopoint == 0) {
+            if (kKep || P.twopoint == 0) {
               AuxBar d;
               chandrashekar_vjp_a(me, ot, nv, c1, w, d);
               ab.rho += d.rho; ab.u[0] += d.u[0]; ab.u[1] += d.u[1]; ab.u[2] += d.u[2];
@@ -637,7 +676,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
               const int tl = line_node<N>(r, l, pp, qq);
               const double cw = sg * sb.winv[l] * L[l];
 #pragma unroll
-              for (int c = 0; c < 3; ++c) jf[c] += L[l] * (AFF ? jr[c] : sja[c * n3 + tl]);
+              for (int c = 0; c < 3; ++c) jf[c] += L[l] * (kAff ? jr[c] : sja[c * n3 + tl]);
 #pragma unroll
               for (int v = 0; v < 5; ++v) W[v] += cw * sl[v * n3 + tl];
             }
@@ -646,7 +685,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
             double om[5], Uf[5];
 #pragma unroll
             for (int v = 0; v < 5; ++v) om[v] = ca * lm[v] - L[a] * W[v];
-            if (AFF || P.twopoint == 0) {
+            if (kKep || P.twopoint == 0) {
               const Aux af = make_aux(qf);
               AuxBar da, dfb;
               chandrashekar_vjp_ab(me, af, nv, c1, om, da, dfb);
@@ -668,7 +707,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
           }
         }
       }
-      if (!AFF || ES) __syncthreads();
+      if (!kAff || ES) __syncthreads();
       if constexpr (ES) {
         // the u~_f parts of this direction's faces, summed along each line
         const double* sred = sB + (8 + kJaV) * n3;
@@ -684,7 +723,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, AFF>())) void
         }
       }
     }
-    if (act && (AFF || P.twopoint == 0)) {
+    if (act && (kKep || P.twopoint == 0)) {
       if (!kPrefetch) load_u();
       const double* u = un;
       const Prim q = cons2prim(u, P.gm1);

@@ -247,12 +247,18 @@ hipError_t DGX_NAME(launch_adjoint)(const Cfg& c, const Geo& g, const Phys& p, c
   const AdjUpd none{nullptr, nullptr, 0.0, 0.0, 0.0};
   const AdjUpd& upv = c.physics == 1 ? none : up;
   const dim3 grid(Shape<kN>::grid(g.nElems)), block(Shape<kN>::block);
-  // volume + surface adjoint
+  // volume + surface adjoint (the variant without the central flux but with
+  // node-array metric terms only on LGL nodes: on Gauss nodes it holds more
+  // registers than the general kernel, N = 7 with 240 B of spills)
 #define DGX_ADJ_V(NODES, FORM, PHYS, ROE, VL)                                                                  \
   do {                                                                                                         \
-    if (FORM == 1 && ROE == 0 && VL == 0 && c.affine && p.twopoint == 0)                                       \
-      hipLaunchKernelGGL((k_adj_volume<kN, NODES, FORM, PHYS, ROE, VL, FORM * (1 - ROE) * (1 - VL)>), grid, block, 0, s, g, \
-                         p, U, lam, Utr, Lbar, gin, gtr, out, qbar, upv);                                      \
+    constexpr int kVar = FORM * (1 - ROE) * (1 - VL);                                                          \
+    if (kVar && p.twopoint == 0 && c.affine)                                                                   \
+      hipLaunchKernelGGL((k_adj_volume<kN, NODES, FORM, PHYS, ROE, VL, kVar>), grid, block, 0, s, g, p, U, lam, Utr, \
+                         Lbar, gin, gtr, out, qbar, upv);                                                      \
+    else if (kVar && NODES == 1 && p.twopoint == 0)                                                            \
+      hipLaunchKernelGGL((k_adj_volume<kN, NODES, FORM, PHYS, ROE, VL, 2 * kVar * NODES>), grid, block, 0, s, g, p, U, lam, \
+                         Utr, Lbar, gin, gtr, out, qbar, upv);                                                 \
     else                                                                                                       \
       hipLaunchKernelGGL((k_adj_volume<kN, NODES, FORM, PHYS, ROE, VL>), grid, block, 0, s, g, p, U, lam, Utr, \
                          Lbar, gin, gtr, out, qbar, upv);                                                      \
