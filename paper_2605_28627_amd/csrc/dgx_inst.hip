@@ -88,12 +88,14 @@ static void vol_mode_r(int mode, int affine, const Geo& g, const Phys& p, const 
 #define DGX_VOL_VAR(MODE, VAR)                                                                                         \
   hipLaunchKernelGGL((k_volume<kN, NODES, FORM, PHYS, PREC, MODE, ROE, 0, VAR>), grid, block, 0, s, g, p, U, Utr, gvn, \
                      gvf, Ut, Uio, dU, Utr_next, A, B, dt)
-      if (affine && mode == 0) DGX_VOL_VAR(0, 1);
-      else if (affine) DGX_VOL_VAR(1, 1);
-      else if (mode == 0) DGX_VOL_VAR(0, 2);
-      else DGX_VOL_VAR(1, 2);
+      // (Gauss nodes without the affine mesh: the general kernel, which holds no
+      // more registers than one without the central flux would: 166 against 168
+      // and spills at N = 3)
+      if (affine && mode == 0) { DGX_VOL_VAR(0, 1); return; }
+      if (affine) { DGX_VOL_VAR(1, 1); return; }
+      if (NODES == 1 && mode == 0) { DGX_VOL_VAR(0, 1 + NODES); return; }
+      if (NODES == 1) { DGX_VOL_VAR(1, 1 + NODES); return; }
 #undef DGX_VOL_VAR
-      return;
     }
   }
   if (mode == 0)
