@@ -69,8 +69,10 @@ __device__ inline void rusanov_prim(const double WL[5], const double WR[5], cons
 // master indexing) from their two layers: each side's first layer plus half
 // its limited outward slope, the other side's first layer as ghost; and the
 // master-outward sub-face vector S.
+// (Wm, optional: the first layer of slot mo as it is.)
 __device__ inline void fv_face_states(const double* __restrict__ Utr, const double* __restrict__ fvSb, int nS, int n2,
-                                      int side, int fi, double W0f[5], double W1f[5], double S[3]) {
+                                      int side, int fi, double W0f[5], double W1f[5], double S[3], int mo = 0,
+                                      double* Wm = nullptr) {
   double W0[2][5];
 #pragma unroll
   for (int m = 0; m < 2; ++m)
@@ -82,6 +84,7 @@ __device__ inline void fv_face_states(const double* __restrict__ Utr, const doub
     const double w11 = Utr[tr_index(1, 5 + v, kTrFV, nS, side, n2, fi)];
     W0f[v] = W0[0][v] + 0.5 * minmod(W0[0][v] - w10, W0[1][v] - W0[0][v]);
     W1f[v] = W0[1][v] + 0.5 * minmod(W0[1][v] - w11, W0[0][v] - W0[1][v]);
+    if (Wm) Wm[v] = mo ? W0[1][v] : W0[0][v];
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) S[c] = fvSb[((size_t)c * nS + side) * n2 + fi];
@@ -421,8 +424,10 @@ __global__ __launch_bounds__(Shape<N>::block) void k_lift_fv(Geo G, Phys P, cons
 // both sub-cells' viscous fluxes; the gradients come from k_lift_fv (gin,
 // and gtr2 for the element faces).
 // ---------------------------------------------------------------------------
+// Three waves per SIMD at N = 3, Navier-Stokes (165 VGPRs, no spills; left to
+// itself the compiler takes 183 and two waves: 32^3 half FV 4.47 -> 4.34 ms).
 template <int N, int MODE, int PHYS = 0>
-__global__ __launch_bounds__(Shape<N>::block) void k_fv(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block, PHYS == 1 && N == 3 ? 3 : 1) void k_fv(Geo G, Phys P, const double* __restrict__ U,
                                                       const double* __restrict__ Utr, const double* __restrict__ gin,
                                                       const double* __restrict__ gtr2, double* __restrict__ Ut,
                                                       double* __restrict__ Uio, double* __restrict__ dU,
@@ -434,16 +439,22 @@ __global__ __launch_bounds__(Shape<N>::block) void k_fv(Geo G, Phys P, const dou
   constexpr int n1 = S::n1, n2 = S::n2, n3 = S::n3;
   if (!G.etype[e]) return;   // DG elements belong to the residual kernel
   const int nE = G.nElems, nS = G.nSides;
+  // An element inside one wavefront passes the gradients of a sub-cell's lower
+  // neighbour by shuffle and reuses the slopes' tile for the fluxes (its
+  // barriers cost nothing): 12.7 KB of LDS at N = 3, as many elements per CU as
+  // the registers allow.
+  constexpr bool kWave = S::nth <= 64;
   __shared__ double sw_s[S::epb * (5 * n3)];
   double* const sw = sw_s + ib * (5 * n3);
   __shared__ double ssl_s[S::epb * (5 * n3)];
   double* const ssl = ssl_s + ib * (5 * n3);
-  __shared__ double sfl_s[S::epb * (5 * n3)];
-  double* const sfl = sfl_s + ib * (5 * n3);
-  __shared__ double sfe_s[S::epb * (3 * 5 * n2)];   // outward fluxes through the upper element faces 1, 3, 5
-  double* const sfe = sfe_s + ib * (3 * 5 * n2);
-  __shared__ double sgr_s[S::epb * (PHYS == 1 ? 12 * n3 : 1)];   // sub-cell gradients
-  double* const sgr = sgr_s + ib * (PHYS == 1 ? 12 * n3 : 1);
+  __shared__ double sfl_own[kWave ? 1 : 5 * n3];
+  double* const sfl = kWave ? ssl : sfl_own;
+  __shared__ double sfe_s[S::epb * (6 * 5 * n2)];   // outward fluxes through the element faces
+  double* const sfe = sfe_s + ib * (6 * 5 * n2);
+  __shared__ double sgh_s[S::epb * (6 * 5 * n2)];   // the neighbours' first layers (ghost cells)
+  double* const sgh = sgh_s + ib * (6 * 5 * n2);
+  __shared__ double sgr[PHYS == 1 && !kWave ? 12 * n3 : 1];   // sub-cell gradients
   const bool act = t < n3;
   const int i = t % n1, j = (t / n1) % n1, k = t / n2;
   const int idx[3] = {i, j, k};
@@ -458,26 +469,33 @@ __global__ __launch_bounds__(Shape<N>::block) void k_fv(Geo G, Phys P, const dou
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
         gme[c] = gin[((size_t)c * nE + e) * n3 + t];
-        sgr[c * n3 + t] = gme[c];
+        if (!kWave) sgr[c * n3 + t] = gme[c];
       }
     }
   }
-  // Fluxes through the three upper element faces (their loads overlap the
-  // state's).  The lower element face of each line rides along with the
-  // interior sub-faces below, so every direction takes one flux pass.
-  for (int ft = t; ft < 3 * n2; ft += S::nth) {
-    const int r = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1;
-    const int info = G.efc[e * 6 + 2 * r + 1];
+  // Fluxes through all six element faces, their face nodes on consecutive
+  // work-items, and the neighbours' first layers, which both reads share: two
+  // dense passes at N = 3 and no trace is read again below.  With the lower
+  // faces formed beside the interior sub-faces of each direction (by the first
+  // sub-cell of each line, 1 work-item in 4) every direction ran both flux
+  // codes and waited for its own traces.
+#pragma unroll 1
+  for (int ft = t; ft < S::nface; ft += S::nth) {
+    const int f = face_of<N>(ft), rr = ft % n2, pp = rr % n1, qq = rr / n1;
+    const int info = G.efc[e * 6 + f];
     const int side = efc_side(info), slot = efc_slot(info);
     int p = pp, qm = qq;
     if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
-    double F[5], W0f[5], W1f[5], Sv[3];
-    fv_face_states(Utr, G.fvSb, nS, n2, side, qm * n1 + p, W0f, W1f, Sv);
+    const int fi = qm * n1 + p;
+    double F[5], W0f[5], W1f[5], Wo[5], Sv[3];
+    fv_face_states(Utr, G.fvSb, nS, n2, side, fi, W0f, W1f, Sv, 1 - slot, Wo);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) sgh[(f * 5 + v) * n2 + rr] = Wo[v];
     rusanov_prim(W0f, W1f, Sv, P, F);
-    if constexpr (PHYS == 1) fv_face_visc(Utr, gtr2, nS, n2, side, qm * n1 + p, Sv, P, F);
+    if constexpr (PHYS == 1) fv_face_visc(Utr, gtr2, nS, n2, side, fi, Sv, P, F);
     const double sg = slot ? -1.0 : 1.0;   // outward
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sfe[(r * 5 + v) * n2 + rr] = sg * F[v];
+    for (int v = 0; v < 5; ++v) sfe[(f * 5 + v) * n2 + rr] = sg * F[v];
   }
   if (act) {
     cons_to_prim5(u, P.gm1, W);
@@ -491,67 +509,59 @@ __global__ __launch_bounds__(Shape<N>::block) void k_fv(Geo G, Phys P, const dou
     const int pp = r == 0 ? j : i, qq = r == 2 ? j : k;
     const int rr = qq * n1 + pp;
     const int str = r == 0 ? 1 : (r == 1 ? n1 : n2);
-    // master index and slot of this line's two element faces
-    int fi[2], side[2], slot[2];
-#pragma unroll
-    for (int end = 0; end < 2; ++end) {
-      const int info = G.efc[e * 6 + 2 * r + end];
-      side[end] = efc_side(info); slot[end] = efc_slot(info);
-      int p = pp, qm = qq;
-      if (slot[end]) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
-      fi[end] = qm * n1 + p;
-    }
+    double Sv[3] = {0, 0, 0};   // lower interior sub-face (a-1 | a) along +xi_r
     if (act) {
-      double Wm[5], Wp[5];
+      if (a > 0) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        Wm[v] = a > 0 ? sw[v * n3 + t - str] : Utr[tr_index(1 - slot[0], v, kTrFV, nS, side[0], n2, fi[0])];
-        Wp[v] = a < N ? sw[v * n3 + t + str] : Utr[tr_index(1 - slot[1], v, kTrFV, nS, side[1], n2, fi[1])];
-        ssl[v * n3 + t] = minmod(Wp[v] - W[v], W[v] - Wm[v]);
+        for (int c = 0; c < 3; ++c) Sv[c] = G.fvS[(((size_t)(3 * r + c) * nE + e) * N + a - 1) * n2 + rr];
       }
+      const double* pm = a > 0 ? sw + (t - str) : sgh + (2 * r) * 5 * n2 + rr;
+      const double* pq = a < N ? sw + (t + str) : sgh + (2 * r + 1) * 5 * n2 + rr;
+      const int sm = a > 0 ? n3 : n2, sp = a < N ? n3 : n2;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) ssl[v * n3 + t] = minmod(pq[v * sp] - W[v], W[v] - pm[v * sm]);
     }
     __syncthreads();
+    double F[5] = {0, 0, 0, 0, 0}, gl[PHYS == 1 ? 12 : 1];
+    if constexpr (PHYS == 1 && kWave) {
+      const int lane = (int)threadIdx.x & 63;
+#pragma unroll
+      for (int c = 0; c < 12; ++c) gl[c] = __shfl(gme[c], lane - str);
+    }
     if (act) {
-      // the flux through the lower face of sub-cell a: the interior sub-face
-      // (a-1 | a) along +xi_r, or for a = 0 the element face (master-outward)
-      double WL[5], WR[5], Sv[3];
       if (a > 0) {
+        double WL[5], WR[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
           WL[v] = sw[v * n3 + t - str] + 0.5 * ssl[v * n3 + t - str];
           WR[v] = W[v] - 0.5 * ssl[v * n3 + t];
         }
-#pragma unroll
-        for (int c = 0; c < 3; ++c) Sv[c] = G.fvS[(((size_t)(3 * r + c) * nE + e) * N + a - 1) * n2 + rr];
-      } else {
-        fv_face_states(Utr, G.fvSb, nS, n2, side[0], fi[0], WL, WR, Sv);
-      }
-      double F[5];
-      rusanov_prim(WL, WR, Sv, P, F);
-      if constexpr (PHYS == 1) {
-        if (a > 0) {
+        rusanov_prim(WL, WR, Sv, P, F);
+        if constexpr (PHYS == 1) {
           // central mean of the two sub-cells' viscous fluxes (cell means and gradients)
-          double Wl[5], gl[12], Gl[4], Gr[4];
+          double Wl[5], Gl[4], Gr[4];
 #pragma unroll
           for (int v = 0; v < 5; ++v) Wl[v] = sw[v * n3 + t - str];
+          if constexpr (!kWave) {
 #pragma unroll
-          for (int c = 0; c < 12; ++c) gl[c] = sgr[c * n3 + t - str];
+            for (int c = 0; c < 12; ++c) gl[c] = sgr[c * n3 + t - str];
+          }
           viscous_flux<double, 0>(prim_of_w(Wl), gl, P, Sv, Gl);
           viscous_flux<double, 0>(prim_of_w(W), gme, P, Sv, Gr);
 #pragma unroll
           for (int v = 0; v < 4; ++v) F[1 + v] -= 0.5 * (Gl[v] + Gr[v]);
-        } else {
-          fv_face_visc(Utr, gtr2, nS, n2, side[0], fi[0], Sv, P, F);
         }
-      }
-      if (a > 0) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) { sfl[v * n3 + t] = F[v]; acc[v] += F[v]; }
+        for (int v = 0; v < 5; ++v) acc[v] += F[v];
       } else {
-        const double sg = slot[0] ? -1.0 : 1.0;   // outward
 #pragma unroll
-        for (int v = 0; v < 5; ++v) acc[v] -= sg * F[v];
+        for (int v = 0; v < 5; ++v) acc[v] -= sfe[(2 * r * 5 + v) * n2 + rr];
       }
+    }
+    if constexpr (kWave) __syncthreads();   // (the slopes are read)
+    if (act && a > 0) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sfl[v * n3 + t] = F[v];
     }
     __syncthreads();
     if (act) {
@@ -560,10 +570,11 @@ __global__ __launch_bounds__(Shape<N>::block) void k_fv(Geo G, Phys P, const dou
         for (int v = 0; v < 5; ++v) acc[v] -= sfl[v * n3 + t + str];
       } else {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) acc[v] -= sfe[(r * 5 + v) * n2 + rr];
+        for (int v = 0; v < 5; ++v) acc[v] -= sfe[((2 * r + 1) * 5 + v) * n2 + rr];
       }
     }
-    // (no barrier: the next direction writes sfl only after its slope barrier)
+    // (several wavefronts: the next direction writes sfl only after its slope barrier)
+    if constexpr (kWave) __syncthreads();
   }
   double Unew[5];
   if (act) {
