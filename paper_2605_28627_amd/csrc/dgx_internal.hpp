@@ -14,6 +14,13 @@ constexpr int kMaxN = 7;
 constexpr int kMaxN1 = kMaxN + 1;
 
 // Device copy of the 1-D operators of one context (all FP64).
+// Lobatto nodes in double: the lifting adds its own side's half of the viscous
+// surface flux to the viscous volume term at the face nodes, where the residual
+// kernel used to subtract it again from both sides' fluxes; that kernel then
+// reads the other side's flux only (24 B per node less at N = 7).  The float
+// mode keeps both in the surface flux, rounded as it stores them.
+constexpr bool own_visc_in_volume(int nodes, int prec) { return nodes == 1 && prec == 0; }
+
 struct DevBasis {
   double w[kMaxN1];               // quadrature weights
   double winv[kMaxN1];            // 1 / w

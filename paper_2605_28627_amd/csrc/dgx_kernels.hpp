@@ -483,6 +483,8 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
       for (int c = 0; c < 12; ++c) gout[((size_t)c * nE + e) * n3 + t] = acc[c];
     }
   }
+  constexpr bool kOwnV = EMIT == 1 && own_visc_in_volume(NODES, PREC);
+  double vv[4] = {0.0, 0.0, 0.0, 0.0};   // the viscous volume term
   if constexpr (EMIT == 1) {
     // Viscous part of the volume term: G~^r at every node into LDS (the
     // gradient sweep's q and Ja tiles are dead once every work-item is past
@@ -505,7 +507,6 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
     __syncthreads();
     if (act) {
       const int idx[3] = {i, j, k};
-      double vv[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
         const int a = idx[r];
@@ -518,12 +519,14 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
           for (int v = 0; v < 4; ++v) vv[v] -= c * sG[(4 * r + v) * n3 + tl];
         }
       }
+      if constexpr (!kOwnV) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) gout[((size_t)v * nE + e) * n3 + t] = vv[v];
+        for (int v = 0; v < 4; ++v) gout[((size_t)v * nE + e) * n3 + t] = vv[v];
+      }
     }
   }
   // face-normal viscous flux of one side from its state trace qt and gradient trace gf
-  auto emit_face = [&](int info, int slot, int side, int fi, const Prim& qt, const double gf[12]) {
+  auto emit_face = [&](int info, int slot, int side, int fi, const Prim& qt, const double gf[12], double wi) {
     const FaceGeom fg = face_geom(G, info, n2, fi);
     const double nh[3] = {fg(0), fg(1), fg(2)};
     const double s = fg(3);
@@ -532,6 +535,11 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
     viscous_flux<FT, VL>(qt, gf, P, nv, Gn);
 #pragma unroll
     for (int v = 0; v < 4; ++v) st_visc<PREC>(gtr, tr_index(slot, v, 4, nS, side, n2, fi), Gn[v]);
+    if constexpr (kOwnV) {
+      const double cw = (slot ? -0.5 : 0.5) * wi;   // (wi = 1/w at the face node)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) vv[v] += cw * Gn[v];
+    }
   };
   // gradient traces (LGL, EMIT 0: none, the nodes' gradients are read instead)
   if constexpr (NODES == 1) {
@@ -548,7 +556,11 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
         const int side = efc_side(info), slot = efc_slot(info);
         int p = pp, qm = qq;
         if (slot) orient_to_master(efc_orient(info), N, pp, qq, p, qm);
-        emit_face(info, slot, side, qm * n1 + p, q, acc);   // LGL: the node's state is its trace
+        emit_face(info, slot, side, qm * n1 + p, q, acc, sb.winv[a]);   // LGL: the node's state is its trace
+      }
+      if constexpr (kOwnV) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gout[((size_t)v * nE + e) * n3 + t] = vv[v];
       }
     }
   } else {
@@ -590,7 +602,7 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
           for (int v = 0; v < 5; ++v) ut[v] = Utr[tr_index(slot, v, TNV, nS, side, n2, qm * n1 + p)];
           fq[it] = cons2prim(ut, P.gm1);
         }
-        emit_face(info, slot, side, qm * n1 + p, fq[it], gf);
+        emit_face(info, slot, side, qm * n1 + p, fq[it], gf, 0.0);
       }
     }
   }
@@ -917,11 +929,15 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM, VAR>
       d[4 * n2] = own.beta; d[5 * n2] = own.lrho; d[6 * n2] = own.lbeta; d[7 * n2] = own.k;
     }
     if constexpr (PHYS == 1) {
-      // face-normal viscous fluxes of the two sides, formed by the lifting
+      // face-normal viscous fluxes of the two sides, formed by the lifting (the
+      // own one may already be in its volume term)
 #pragma unroll
-      for (int sd = 0; sd < 2; ++sd)
+      for (int sd = 0; sd < 2; ++sd) {
+        if (own_visc_in_volume(NODES, PREC) && sd == 1) continue;
+        const int ss = own_visc_in_volume(NODES, PREC) ? 1 - slot : sd;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) Phi[1 + v] -= 0.5 * ld_visc<PREC>(gvf, tr_index(sd, v, 4, nS, side, n2, fi));
+        for (int v = 0; v < 4; ++v) Phi[1 + v] -= 0.5 * ld_visc<PREC>(gvf, tr_index(ss, v, 4, nS, side, n2, fi));
+      }
     }
     const double sgn = slot ? -1.0 : 1.0;
 #pragma unroll
