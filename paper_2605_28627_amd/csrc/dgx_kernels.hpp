@@ -227,15 +227,12 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
   // read from the LDS tile (the same bits its trace would give) and only the
   // other side's trace comes from memory; on LG nodes both traces are read.
   // UO holds the other side's trace (LGL) or the master's (LG), UR the slave's (LG).
-  // (Gauss nodes: the own side's primitive trace is returned for the face
-  // fluxes at the end, which read the trace a second time before.)
-  auto face_avg = [&](int ft, int slot, const double UO[5], const double UR[5], const double nsf[4], Prim& own) {
+  auto face_avg = [&](int ft, int slot, const double UO[5], const double UR[5], const double nsf[4]) {
     const int f = face_of<N>(ft), rr = ft % n2;
     double qa[4], qb[4];
     {
       const Prim a = cons2prim(UO, P.gm1);
       qa[0] = a.u[0]; qa[1] = a.u[1]; qa[2] = a.u[2]; qa[3] = a.p / (a.rho * P.R);
-      if constexpr (NODES == 0) own = a;
     }
     if constexpr (NODES == 1) {
       const int pp = rr % n1, qq = rr / n1, r = f / 2;
@@ -245,7 +242,6 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
     } else {
       const Prim b = cons2prim(UR, P.gm1);
       qb[0] = b.u[0]; qb[1] = b.u[1]; qb[2] = b.u[2]; qb[3] = b.p / (b.rho * P.R);
-      if (slot) own = b;
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) sf[(f * 7 + c) * n2 + rr] = 0.5 * (qa[c] + qb[c]);
@@ -279,7 +275,6 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
   constexpr bool kOneFaceNode = S::nface <= S::nth;
   double u[5] = {0, 0, 0, 0, 0}, jl[9];
   double fUL[5], fUR[5], fns[4];
-  Prim fq[kFI];   // (Gauss nodes) the own primitive traces of this work-item's face nodes
   int fslot = 0;
   const NodeMetric nm = node_metric(G, e, n3, t);
   const bool elm = AFF || G.em[(size_t)9 * nE + e] > 0.0;   // constant metric terms (uniform)
@@ -334,8 +329,7 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
         int slot;
         double UL[5], UR[5], nsf[4];
         face_load(ft, G.efc[e * 6 + f], slot, UL, UR, nsf);
-        Prim qo;
-        face_avg(ft, slot, UL, UR, nsf, qo);
+        face_avg(ft, slot, UL, UR, nsf);
         continue;
       }
       const int pp = rr % n1, qq = rr / n1, r = f / 2;
@@ -397,7 +391,7 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
       }
     }
   } else if constexpr (kOneFaceNode) {
-    if (t < S::nface) face_avg(t, fslot, fUL, fUR, fns, fq[0]);
+    if (t < S::nface) face_avg(t, fslot, fUL, fUR, fns);
   } else {
 #pragma unroll
     for (int it = 0; it < kFI; ++it) {
@@ -406,7 +400,7 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
       int slot;
       double UL[5], UR[5], nsf[4];
       face_load(ft, finfo[it], slot, UL, UR, nsf);
-      face_avg(ft, slot, UL, UR, nsf, fq[it]);
+      face_avg(ft, slot, UL, UR, nsf);
     }
   }
   __syncthreads();
@@ -596,13 +590,10 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
           for (int a = 0; a < n1; ++a) s += L[a] * sm[c * n3 + line_node<N>(r, a, pp, qq)];
           gf[c] = s;
         }
-        if constexpr (kFvf) {
-          double ut[5];
+        double ut[5];
 #pragma unroll
-          for (int v = 0; v < 5; ++v) ut[v] = Utr[tr_index(slot, v, TNV, nS, side, n2, qm * n1 + p)];
-          fq[it] = cons2prim(ut, P.gm1);
-        }
-        emit_face(info, slot, side, qm * n1 + p, fq[it], gf, 0.0);
+        for (int v = 0; v < 5; ++v) ut[v] = Utr[tr_index(slot, v, TNV, nS, side, n2, qm * n1 + p)];
+        emit_face(info, slot, side, qm * n1 + p, cons2prim(ut, P.gm1), gf, 0.0);
       }
     }
   }
