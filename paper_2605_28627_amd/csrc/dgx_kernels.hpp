@@ -1161,6 +1161,13 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM, VAR>
             of.beta = d[4 * n2]; of.lrho = d[5 * n2]; of.lbeta = d[6 * n2]; of.k = d[7 * n2];
             const double nv[3] = {0.5 * (jr[0] + jf[0]), 0.5 * (jr[1] + jf[1]), 0.5 * (jr[2] + jf[2])};
             two_point(of, nv, Gf[f]);
+            // (F_rho is a product: with no branch around it, as kKep has none, it
+            // would be contracted into the differences below, which the other
+            // variants round separately)
+            if constexpr (kKep) {
+#pragma unroll
+              for (int v = 0; v < 5; ++v) asm volatile("" : "+v"(Gf[f][v]));
+            }
             if (kSymLines && (n1 == 4 || r < 2)) {
               // line sum by a butterfly over the line's lanes (bits of a in the lane id)
               const int str = r == 0 ? 1 : (r == 1 ? n1 : n2);
