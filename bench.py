@@ -199,7 +199,12 @@ ROOF_FAMILIES = ("volume", "fv")
 
 
 def volume_kernel_name(w, precision=0, roe=0):
-    return f"void dgx::k_volume<{w['N']}, {w['nodes']}, {w['form']}, {w['physics']}, {precision}, 1, {roe}, 0>"
+    # (the last parameter: the split form's variants for affine meshes, 1, and,
+    # on Lobatto nodes, for others, 2)
+    var = 0
+    if w["form"] == 1 and not roe:
+        var = 1 if not w["curved"] else (2 if w["nodes"] == 1 else 0)
+    return f"void dgx::k_volume<{w['N']}, {w['nodes']}, {w['form']}, {w['physics']}, {precision}, 1, {roe}, 0, {var}>"
 
 
 def metric_values_per_dof(w, elem_frac=0.0, nvals=10):
@@ -211,7 +216,7 @@ def metric_values_per_dof(w, elem_frac=0.0, nvals=10):
     return nvals * (1.0 - elem_frac) + nvals * elem_frac / n3
 
 
-def volume_kernel_bytes_per_dof(w, precision=0, elem_frac=0.0):
+def volume_kernel_bytes_per_dof(w, precision=0, elem_frac=0.0, merged=False):
     """Compulsory HBM bytes of one launch of the residual/RK kernel, per node.
 
     Reads: U (5), metrics Ja (9) and 1/J (1) (metric_values_per_dof: once per
@@ -223,6 +228,11 @@ def volume_kernel_bytes_per_dof(w, precision=0, elem_frac=0.0):
     kernel.  Writes: dU (5), U (5) and the element's own traces of the new
     state (5 per face node).  8 bytes each, except the face viscous fluxes
     in the FP32-flux mode (4 bytes).
+
+    merged: what the kernels leave out of that table.  On LGL nodes the own
+    trace (it is the face node's state) and, in FP64, the own side's viscous
+    flux (the lifting adds it to the volume term); and for the fraction
+    elem_frac of elements the face geometry per node (once per side there).
     """
     n1 = w["N"] + 1
     fpn = 6 * n1 * n1 / n1 ** 3          # face nodes of one element per volume node
@@ -230,21 +240,29 @@ def volume_kernel_bytes_per_dof(w, precision=0, elem_frac=0.0):
     writes = 5 + 5 + fpn * 5
     if w["physics"] == 1:
         reads += 4 + fpn * 8 * (0.5 if precision == 1 else 1.0)
+    if merged:
+        reads -= elem_frac * fpn * 4 * (1 - 1 / n1 ** 2)
+        if w["nodes"] == 1:
+            reads -= fpn * (5 + (4 if w["physics"] == 1 and precision == 0 else 0))
     return 8.0 * (reads + writes)
 
 
-def lift_kernel_bytes_per_dof(w, precision=0, elem_frac=0.0):
+def lift_kernel_bytes_per_dof(w, precision=0, elem_frac=0.0, merged=False):
     """Compulsory HBM bytes of one launch of the lifting kernel (the forward
     stages' variant), per node.  Reads: U (5), Ja (9), 1/J (1) (as in the
     residual kernel), and per face node the other side's trace (5; on Gauss
     nodes both sides', 2 x 5: on LGL nodes the own trace is the face node's
     state, which the kernel has in LDS) and the face normal + area (4).
     Writes: the viscous volume term (4) and the element's own face-normal
-    viscous flux (4 per face node; 4 bytes each in the FP32-flux mode)."""
+    viscous flux (4 per face node; 4 bytes each in the FP32-flux mode).
+    merged: the fraction elem_frac of elements reads the face geometry once
+    per side."""
     n1 = w["N"] + 1
     fpn = 6 * n1 * n1 / n1 ** 3
     traces = 5 if w["nodes"] == 1 else 10
     reads = 5 + metric_values_per_dof(w, elem_frac) + fpn * (traces + 4)
+    if merged:
+        reads -= elem_frac * fpn * 4 * (1 - 1 / n1 ** 2)
     writes = 4 + fpn * 4 * (0.5 if precision == 1 else 1.0)
     return 8.0 * (reads + writes)
 
@@ -268,7 +286,12 @@ def adjoint_kernel_bytes_per_dof(w, elem_frac=0.0):
       k_adj_lift_volume (Navier-Stokes): 1/J 1, the own trace 5 fpn, both
         Qbar 8 fpn, out 5, lamU 5, lamdU 5; writes lamU and lamdU 10 and the
         next stage's surface adjoint 5 fpn.
-    Ja and 1/J as in the residual kernel (metric_values_per_dof)."""
+    Ja and 1/J as in the residual kernel (metric_values_per_dof).
+    The kernels read less than this table: k_adj_volume takes the own side's
+    gradient alone (on LGL nodes, with the own trace, from the node arrays,
+    and k_lift writes no gradient traces there), k_trace and k_adj_trace are
+    one launch where both are needed, and plane faces have their geometry
+    once per side."""
     n1 = w["N"] + 1
     fpn = 6 * n1 * n1 / n1 ** 3
     ns = w["physics"] == 1
@@ -428,7 +451,7 @@ def main():
     npe = (w["N"] + 1) ** 3
     # (Navier-Stokes FV contexts: the residual kernel reads the node arrays)
     elem_frac = 0.0 if args.fv != "none" and w["physics"] == 1 else n_elem_metric / s.nElems
-    bytes_launch = volume_kernel_bytes_per_dof(w, elem_frac=elem_frac) * (dof - nfv * npe)
+    bytes_launch = volume_kernel_bytes_per_dof(w, elem_frac=elem_frac, merged=nfv == 0) * (dof - nfv * npe)
     kfam = "k_volume"
     if nfv:
         # the roofline of the dominant family: DG elements (k_volume) or FV elements (k_fv)
@@ -499,7 +522,7 @@ def main():
                                                   "from the committed rocprofv3 summary"}
     if lift_n:
         result["kernels_ms_per_launch"]["lift"] = lift_ms / lift_n
-        lb = lift_kernel_bytes_per_dof(w, elem_frac=n_elem_metric / s.nElems) * dof
+        lb = lift_kernel_bytes_per_dof(w, elem_frac=n_elem_metric / s.nElems, merged=True) * dof
         lgbs = lb / (lift_ms * 1e-3 / lift_n) / 1e9
         result["roofline_lift"] = {"bound": "hbm", "kernel": "k_lift (BR1 lifting, forward stages)",
                                    "achieved": lgbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": lgbs / HBM_PEAK_GBS,
