@@ -557,7 +557,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, VAR>())) void
           if (!kAff) sja[c * n3 + t] = jr[c];
         }
       }
-      if (!kAff || r == 0) __syncthreads();
+      if (sweep_begin_barrier(kAff, ES, r)) __syncthreads();
       if (act || kExch) {
         const int a = idx[r];
         const int pp = r == 0 ? j : i, qq = r == 2 ? j : k;
@@ -707,7 +707,7 @@ __global__ __launch_bounds__(Shape<N>::block, (adj_waves<N, NODES, VAR>())) void
           }
         }
       }
-      if (!kAff || ES) __syncthreads();
+      if (sweep_end_barrier(kAff, ES)) __syncthreads();
       if constexpr (ES) {
         // the u~_f parts of this direction's faces, summed along each line
         const double* sred = sB + (8 + kJaV) * n3;

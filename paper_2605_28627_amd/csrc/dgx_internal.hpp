@@ -54,6 +54,16 @@ __host__ __device__ inline void orient_to_master(int o, int N, int pp, int qq, i
   if (o & 4) { p = b; q = a; } else { p = a; q = b; }
 }
 
+// Barriers of the split form's sweep over the directions r = 0, 1, 2 of an
+// element (residual and adjoint): whether its work-items meet before and after
+// the line sums of direction r.  The metric row (unless aff: uniform terms) and
+// on Gauss nodes (es) the face parts of a direction are staged in LDS tiles that
+// the next direction overwrites, while a slower wavefront may still be reading
+// them: both barriers then.  Affine elements on Lobatto nodes stage nothing per
+// direction and need one barrier, behind the records of all nodes.
+constexpr bool sweep_begin_barrier(bool aff, bool es, int r) { return !aff || es || r == 0; }
+constexpr bool sweep_end_barrier(bool aff, bool es) { return !aff || es; }
+
 // Physical constants and switches seen by the kernels.
 struct Phys {
   double gamma, gm1, mu, lam, R, Rinv, Pr;  // lam = mu gamma R / ((gamma-1) Pr): heat conductivity

@@ -710,8 +710,9 @@ constexpr int volume_waves() {
 //
 // VAR 1 (split form, every element of the mesh affine, Chandrashekar's flux):
 // the metric terms are uniform over the workgroup and live in scalar
-// registers; no metric rows in LDS (N = 7: 12 KB), none read per pair, and no
-// barriers between directions whose pairs stay inside a wavefront.  The
+// registers; no metric rows in LDS (N = 7: 12 KB), none read per pair, and on
+// Lobatto nodes no barriers between directions whose pairs stay inside a
+// wavefront (sweep_begin_barrier).  The
 // central two-point flux is compiled out of the pair loops, where it cost 10-20
 // registers as a run-time choice.  N = 7 Navier-Stokes: 105 VGPRs and 66 KB
 // instead of 122 and 78; 32^3 (2 steps) 23.2 -> 22.5 ms, 16^3 (4 steps)
@@ -1037,8 +1038,7 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM, VAR>
 #pragma unroll
         for (int c = 0; c < 3; ++c) sja[c * n3 + t] = jr[c];
       }
-      // (kAff: nothing of the later directions is staged; ES: the face records are)
-      if (!kAff || ES || r == 0) __syncthreads();
+      if (sweep_begin_barrier(kAff, ES, r)) __syncthreads();
       if (act) {
         if (r < 2) fetch_dir(r + 1);
         else fetch_end();
@@ -1206,8 +1206,8 @@ __global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM, VAR>
           }
         }
       }
-      // (kAff, LGL: the tile is read-only from here on; sx has its own barriers)
-      if (!kAff || ES || (MODE == 1 && NODES == 0)) __syncthreads();
+      // (sx has its own barriers)
+      if (sweep_end_barrier(kAff, ES)) __syncthreads();
     } else {
       // weak form: F~^r = Ja^r . f at every node, then the Dhat contraction
       // (the viscous part comes contracted from the lifting kernel)

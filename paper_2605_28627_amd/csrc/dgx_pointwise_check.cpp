@@ -18,6 +18,11 @@ static Phys make_phys(const double* c) {
 
 extern "C" {
 
+// barriers around direction r of the split form's sweep: bit 0 before, bit 1 after its line sums
+int pw_sweep_barriers(int aff, int es, int r) {
+  return (sweep_begin_barrier(aff != 0, es != 0, r) ? 1 : 0) | (sweep_end_barrier(aff != 0, es != 0) ? 2 : 0);
+}
+
 void pw_chandrashekar(const double* Ua, const double* Ub, const double* n, const double* c, double* F) {
   Phys P = make_phys(c);
   Aux a = make_aux(cons2prim(Ua, P.gm1)), b = make_aux(cons2prim(Ub, P.gm1));

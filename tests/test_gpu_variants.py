@@ -146,3 +146,52 @@ def test_packed_elements(S, orc, K, nodes, form, physics):
     finally:
         s.close()
         f.close()
+
+
+@pytest.mark.parametrize("physics", [0, 1])
+@pytest.mark.parametrize("nodes", [0, 1])
+@pytest.mark.parametrize("N", range(1, 8))
+def test_affine_adjoint(S, orc, N, nodes, physics):
+    """The split form's adjoint on an affine mesh, with the library's own
+    (exactly constant) metric terms: against the oracle's tangent, whose terms
+    differ by their rounding dm (the residual is a sum of n1 pairs per line,
+    linear in Ja and 1/J, the viscous part quadratic in Ja: 20 dm covers it),
+    and entry by entry against the kernels that read the node arrays."""
+    _say("affine adjoint", N, nodes, physics)
+    mesh = I.box_mesh((2, 2, 2), (-PI,) * 3, (PI,) * 3, rotate_seed=5)
+    cfg = dict(N=N, nodes=nodes, form=1, physics=physics, mu=0.05 if physics else 0.0)
+    o, s = orc.Oracle(cfg, mesh), S(cfg, mesh, adjoint=True)
+    try:
+        assert s.element_metric_count() == mesh.nElems
+        _, Ja, sJ, nv = s.metrics()
+        _, J, Jo = o.geometry()
+        dm = max(np.abs(Ja.reshape(Jo.shape) - Jo).max() / np.abs(Jo).max(),
+                 np.abs(sJ.reshape(J.shape) * J - 1.0).max(),
+                 np.abs(nv.ravel() - o.face_normals().ravel()).max() / np.abs(nv).max())
+        # (both branches of the log means; the Gauss split form's projected
+        # traces stay positive at this amplitude)
+        U0 = I.smooth_random_state(o.coords(), 75, amp=0.1)
+        U0[:, : mesh.nElems // 2] = I.smooth_random_state(o.coords(), 75, amp=0.002)[:, : mesh.nElems // 2]
+        rng = np.random.default_rng(76)
+        lam, d = rng.normal(size=U0.shape), rng.normal(size=U0.shape)
+        U = s.init_state(U0)
+        dt = 0.2 * s.timestep(U, 0.9)
+
+        def run():
+            lamU, lamdU = s.to_device(lam), s.empty_state()
+            out = s.adjoint_rhs(U, lamU).cpu().numpy()
+            s.adjoint_rk_step(U, lamU, lamdU, dt)
+            return out, lamU.cpu().numpy()
+
+        on = run()
+        s.set_element_metrics(False)
+        off = run()
+    finally:
+        s.close()
+    _, jd = o.rhs_jvp(U0, d)
+    err = abs((on[0] * d).sum() - (lam * jd).sum()) / np.abs(lam * jd).sum()
+    _say("affine adjoint", N, nodes, physics, "oracle", err, "metric", dm)
+    assert dm < 1e-12 and err < 1e-12 + 20 * dm
+    for a, b in zip(on, off):
+        assert np.isfinite(a).all()
+        assert np.abs(a - b).max() <= 1e-12 * np.abs(b).max()

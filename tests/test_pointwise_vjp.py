@@ -276,3 +276,30 @@ def test_entropy_projection_vjps(pw):
         ref = fd_dot(lambda x: call(pw.pw_entropy_to_cons, 5, x, C), v, d, w, eps=1e-7)
         assert abs(call(pw.pw_entropy_to_cons_vjp, 5, v, C, w) @ d - ref) < 1e-7 * (1 + abs(ref))
 
+
+
+@pytest.mark.parametrize("aff", [0, 1])
+@pytest.mark.parametrize("es", [0, 1])
+def test_sweep_barriers_order_every_shared_tile(pw, aff, es):
+    """The split form's sweep over the directions, as the accesses of one
+    wavefront to the LDS tiles: a write and a read of the same tile, in either
+    order, have to lie on two sides of a barrier, since they may be different
+    wavefronts'."""
+    acc, epoch = [("aux", "w", 0)], 0                  # (tile, kind, barriers passed)
+    for r in range(3):
+        b = pw.pw_sweep_barriers(aff, es, r)
+        if not aff:
+            acc.append(("metric row", "w", epoch))
+        epoch += b & 1
+        acc.append(("aux", "r", epoch))
+        if not aff:
+            acc.append(("metric row", "r", epoch))
+        if es:
+            acc.append(("face parts", "w", epoch))     # each node its own, summed along the lines below
+        epoch += b >> 1
+        if es:
+            acc.append(("face parts", "r", epoch))
+    for n, (tile, kind, e) in enumerate(acc):
+        for tile2, kind2, e2 in acc[n + 1:]:
+            if tile == tile2 and kind != kind2:        # (each work-item writes its own entries only)
+                assert e != e2, (tile, kind, kind2, e)
