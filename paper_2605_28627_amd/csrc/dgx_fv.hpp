@@ -440,16 +440,24 @@ __global__ __launch_bounds__(Shape<N>::block, PHYS == 1 && N == 3 ? 3 : 1) void 
   if (!G.etype[e]) return;   // DG elements belong to the residual kernel
   const int nE = G.nElems, nS = G.nSides;
   // An element inside one wavefront passes the gradients of a sub-cell's lower
-  // neighbour by shuffle and reuses the slopes' tile for the fluxes (its
-  // barriers cost nothing): 12.7 KB of LDS at N = 3, as many elements per CU as
-  // the registers allow.
+  // neighbour by shuffle.
   constexpr bool kWave = S::nth <= 64;
+  // One tile for the slopes and then the fluxes, at the price of two barriers
+  // per direction (none inside one wavefront: 12.7 KB of LDS at N = 3, as many
+  // elements per CU as the registers allow).  Euler, several wavefronts: the
+  // face fluxes and ghost layers leave no room for a tile of each at N = 7,
+  // where 92 KB for one element per CU instead of 72 KB for two took 4.73
+  // instead of 3.49 ms (18^3, half FV, 2 steps), N = 6, 21^3: 11.70 instead of
+  // 10.06 ms; meshes of 4^3 lose 1-2 %.  Navier-Stokes: its gradients' tile
+  // decides, both ways within 1 %.
+  constexpr bool kTile = kWave || PHYS == 0;
+  static_assert(PHYS == 1 || 2 * 8 * S::epb * ((kTile ? 10 : 15) * n3 + 60 * n2) <= 160 * 1024, "two elements per CU");
   __shared__ double sw_s[S::epb * (5 * n3)];
   double* const sw = sw_s + ib * (5 * n3);
   __shared__ double ssl_s[S::epb * (5 * n3)];
   double* const ssl = ssl_s + ib * (5 * n3);
-  __shared__ double sfl_own[kWave ? 1 : 5 * n3];
-  double* const sfl = kWave ? ssl : sfl_own;
+  __shared__ double sfl_own[kTile ? 1 : 5 * n3];
+  double* const sfl = kTile ? ssl : sfl_own;
   __shared__ double sfe_s[S::epb * (6 * 5 * n2)];   // outward fluxes through the element faces
   double* const sfe = sfe_s + ib * (6 * 5 * n2);
   __shared__ double sgh_s[S::epb * (6 * 5 * n2)];   // the neighbours' first layers (ghost cells)
@@ -558,7 +566,7 @@ __global__ __launch_bounds__(Shape<N>::block, PHYS == 1 && N == 3 ? 3 : 1) void 
         for (int v = 0; v < 5; ++v) acc[v] -= sfe[(2 * r * 5 + v) * n2 + rr];
       }
     }
-    if constexpr (kWave) __syncthreads();   // (the slopes are read)
+    if constexpr (kTile) __syncthreads();   // (the slopes are read)
     if (act && a > 0) {
 #pragma unroll
       for (int v = 0; v < 5; ++v) sfl[v * n3 + t] = F[v];
@@ -573,8 +581,8 @@ __global__ __launch_bounds__(Shape<N>::block, PHYS == 1 && N == 3 ? 3 : 1) void 
         for (int v = 0; v < 5; ++v) acc[v] -= sfe[((2 * r + 1) * 5 + v) * n2 + rr];
       }
     }
-    // (several wavefronts: the next direction writes sfl only after its slope barrier)
-    if constexpr (kWave) __syncthreads();
+    // (a tile of their own: the next direction writes sfl only after its slope barrier)
+    if constexpr (kTile) __syncthreads();
   }
   double Unew[5];
   if (act) {
