@@ -167,7 +167,8 @@ dg_status dg_get_metrics(const dg_ctx* ctx, double* xyz, double* Ja, double* sJ,
  * node-array path, Navier-Stokes results agree to rounding.  On by default; enable = 0
  * sends every element to the node arrays (the paper's per-node storage).
  * Takes effect at once when a mesh is on the device, else at its upload;
- * metrics replaced by dg_upload_metrics are examined again. */
+ * metrics replaced by dg_upload_metrics are examined again.  Captured calls
+ * look at the terms when they are replayed. */
 dg_status dg_set_element_metrics(dg_ctx* ctx, int enable);
 
 /* Number of elements whose kernels read the per-element metric terms.

@@ -966,14 +966,26 @@ static dg_status ready(dg_ctx* c, const char* who) {
   return DG_OK;
 }
 
-static Cfg kcfg(const dg_ctx* c) {
+// Whether launches on s go into a graph.  (The default stream cannot be captured,
+// and asking it would fail while another stream is.)
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
+// s: the stream of the launch, for kernels with a variant for affine meshes.
+// Captured launches take the kernels that look at each element's metric terms
+// on the device: a graph replayed after dg_upload_metrics or
+// dg_set_element_metrics reads the terms of that time, which need not be the
+// uniform ones it was captured with.
+static Cfg kcfg(const dg_ctx* c, hipStream_t s = nullptr) {
   Cfg k;
   k.N = c->N; k.nodes = c->cfg.nodes; k.form = c->cfg.volume_form; k.physics = c->cfg.physics;
   k.precision = c->cfg.precision;
   k.roe = c->cfg.riemann == DG_RIEMANN_ROE ? 1 : 0;
   k.visc = c->cfg.viscosity == DG_VISC_SUTHERLAND ? 1 : 0;
   k.fv = c->cfg.fv;
-  k.affine = c->n_const_metric == c->nElems && c->n_const_side == c->nSides;
+  k.affine = c->n_const_metric == c->nElems && c->n_const_side == c->nSides && !capturing(s);
   return k;
 }
 
@@ -1007,7 +1019,7 @@ static Work kwork(const dg_ctx* c) {
 // One residual evaluation whose traces of U already sit in Utr[cur].
 static dg_status stage(dg_ctx* c, int mode, const double* U, double* Ut, double* Uio, double* dU, int cur, double A,
                        double B, double dt, hipStream_t s) {
-  Cfg k = kcfg(c);
+  Cfg k = kcfg(c, s);
   Geo g = kgeo(c);
   Work w = kwork(c);
   if (c->cfg.physics == DG_PHYS_NAVIER_STOKES) {
@@ -1056,7 +1068,7 @@ dg_status dg_lift(dg_ctx* c, const double* U, double* gout, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   Work w = kwork(c);
   LAUNCHCHK(c, launch_trace(kcfg(c), kgeo(c), c->phys, U, w.Utr[0], s));
-  LAUNCHCHK(c, launch_lift(kcfg(c), 0, kgeo(c), c->phys, U, w.Utr[0], gout, w.gtr, s));
+  LAUNCHCHK(c, launch_lift(kcfg(c, s), 0, kgeo(c), c->phys, U, w.Utr[0], gout, w.gtr, s));
   return DG_OK;
 }
 
@@ -1158,7 +1170,7 @@ static dg_status ready_adjoint(dg_ctx* c, const char* who) {
 static dg_status adjoint_residual(dg_ctx* c, const double* U, double* lam, double* out, hipStream_t s, bool begin,
                                   const double* src = nullptr, double scale = 1.0,
                                   const AdjUpd& up = AdjUpd{nullptr, nullptr, 0.0, 0.0, 0.0}) {
-  Cfg k = kcfg(c);
+  Cfg k = kcfg(c, s);
   Geo g = kgeo(c);
   Work w = kwork(c);
   WsLayout L = ws_layout(c);
