@@ -843,13 +843,15 @@ __host__ __device__ inline void surface_flux_vjp_own(const double Uo[5], const d
       Ub[v] += hs * Phib[v];
       lb += Phib[v] * (Uo[v] - Un[v]);
     }
-    lb *= mine ? (side ? -0.5 : 0.5) * s : 0.0;
-    const double sg = uno >= 0.0 ? lb : -lb;
-    const double ub[3] = {sg * nh[0], sg * nh[1], sg * nh[2]};
-    const double pb = lb * P.gamma * ro * 0.5 * rcp_nr(co);
-    double Up[5];
-    prim_vjp(qo, P.gm1, -pb * qo.p * ro, ub, pb, Up);
-    for (int v = 0; v < 5; ++v) Ub[v] += Up[v];
+    if (mine) {   // (the other side's speed may have no derivative: c = 0 or undefined)
+      lb *= (side ? -0.5 : 0.5) * s;
+      const double sg = uno >= 0.0 ? lb : -lb;
+      const double ub[3] = {sg * nh[0], sg * nh[1], sg * nh[2]};
+      const double pb = lb * P.gamma * ro * 0.5 * rcp_nr(co);
+      double Up[5];
+      prim_vjp(qo, P.gm1, -pb * qo.p * ro, ub, pb, Up);
+      for (int v = 0; v < 5; ++v) Ub[v] += Up[v];
+    }
   }
   if constexpr (PHYS == 1) {
     const double Gnb[4] = {-0.5 * Phib[1], -0.5 * Phib[2], -0.5 * Phib[3], -0.5 * Phib[4]};

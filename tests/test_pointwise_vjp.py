@@ -230,6 +230,34 @@ def test_surface_flux_vjp(pw, form, phys, riemann):
         assert abs(got - ref) < 1e-6 * (1 + abs(ref)), (it, got, ref)
 
 
+@pytest.mark.parametrize("phys", [0, 1])
+@pytest.mark.parametrize("slow,p", [(0, 0.0), (1, 0.0), (0, -1e-3)])
+def test_surface_flux_vjp_of_the_slower_side(pw, phys, slow, p):
+    """Rusanov's wave speed belongs to one side.  The other's may have no
+    derivative (p = 0: c = 0) or, the master's, be undefined (the forward flux
+    then takes the slave's): it does not enter the slow side's adjoint, which
+    is the central flux's and the dissipation's at a fixed speed.  (Weak form:
+    nothing else of the flux needs a positive pressure.)"""
+    rng = np.random.default_rng(51)
+    fast = np.array([1.0, -0.5, 0.25, 0.0, 2.0])
+    U = [fast, fast]
+    U[slow] = np.array([1.0, 0.5, 0.0, 0.0, 0.125 + p / (G - 1)])   # |m|^2 / 2 rho = 0.125 exactly
+    nh, s, w = np.array([1.0, 0.0, 0.0]), 1.3, rng.normal(size=5)
+    g = [rng.normal(size=12), rng.normal(size=12)]
+    out = []
+    for riemann in (0, 1):
+        c = C.copy()
+        c[4] = riemann
+        b, gb = [np.zeros(5), np.zeros(5)], [np.zeros(12), np.zeros(12)]
+        pw.pw_surface_flux_vjp(0, phys, P(U[0]), P(U[1]), P(g[0]), P(g[1]), P(nh), ctypes.c_double(s), P(c), P(w),
+                               *[x.ctypes.data_as(_dp) for x in b + gb])
+        assert np.isfinite(b).all() and np.isfinite(gb).all()
+        out.append(b[slow])
+    lmax = 0.5 + np.sqrt(G * (G - 1) * (2.0 - 0.5 * (0.5 ** 2 + 0.25 ** 2)))
+    ref = out[1] + (0.5 if slow == 0 else -0.5) * lmax * s * w
+    assert np.allclose(out[0], ref, rtol=1e-14, atol=1e-14 * np.abs(ref).max())
+
+
 def test_fp32_reference_state_rounds_deviations_only(pw):
     """Low-Mach pairs (p ~ 71, small jumps): the float two-point and advective
     fluxes about the reference state (p0, 2 p0/rho0) keep the momentum and
