@@ -258,6 +258,39 @@ def test_surface_flux_vjp_of_the_slower_side(pw, phys, slow, p):
     assert np.allclose(out[0], ref, rtol=1e-14, atol=1e-14 * np.abs(ref).max())
 
 
+def test_surface_flux_vjp_takes_the_forward_branch(pw):
+    """Wave speeds within an ulp or two of each other: the adjoint takes the
+    side that the forward operations, sqrt(gamma p / rho) + |u.n|, find the
+    faster one (the slow side then has no part in the speed)."""
+    rng = np.random.default_rng(52)
+    nh, s = np.array([1.0, 0.0, 0.0]), 1.0
+    wrong = 0
+    for _ in range(300):
+        rho, p, un = rng.uniform(0.5, 2.0, 2), rng.uniform(0.5, 2.0), rng.uniform(-1, 1)
+        U = [np.array([r, r * un, 0.0, 0.0, p * r / rho[0] / (G - 1) + 0.5 * r * un * un]) for r in rho]
+
+        def speed(V):                                # cons2prim and the speed, in the library's order
+            ri = 1.0 / V[0]
+            u = V[1:4] * ri
+            q = (G - 1.0) * (V[4] - 0.5 * V[0] * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]))
+            return abs(u[0]) + np.sqrt(G * q / V[0])
+
+        lL, lR = speed(U[0]), speed(U[1])
+        slow = 1 if lL >= lR else 0
+        w, z = rng.normal(size=5), np.zeros(12)
+        out = []
+        for riemann in (0, 1):
+            c = C.copy()
+            c[4] = riemann
+            b = [np.zeros(5), np.zeros(5)]
+            pw.pw_surface_flux_vjp(0, 0, P(U[0]), P(U[1]), P(z), P(z), P(nh), ctypes.c_double(s), P(c), P(w),
+                                   *[x.ctypes.data_as(_dp) for x in b + [np.zeros(12), np.zeros(12)]])
+            out.append(b[slow])
+        ref = out[1] + (0.5 if slow == 0 else -0.5) * max(lL, lR) * s * w
+        wrong += not np.allclose(out[0], ref, rtol=1e-13, atol=1e-13)
+    assert wrong == 0
+
+
 def test_fp32_reference_state_rounds_deviations_only(pw):
     """Low-Mach pairs (p ~ 71, small jumps): the float two-point and advective
     fluxes about the reference state (p0, 2 p0/rho0) keep the momentum and
