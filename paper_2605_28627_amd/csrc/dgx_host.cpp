@@ -11,6 +11,8 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <exception>
+#include <functional>
 #include <string>
 #include <thread>
 #include <vector>
@@ -238,6 +240,22 @@ static int host_threads(int nitems, int grain) {
   if (hw > 16) hw = 16;
   int n = nitems / grain;
   return n < 1 ? 1 : (n < hw ? n : hw);
+}
+
+// f(0) .. f(n-1), each on a thread of its own; where no more threads can be had,
+// the rest on the calling one.  (An exception of the thread library must not
+// leave a C entry point, nor end the process with threads unjoined.)
+template <class F>
+static void on_threads(int n, const F& f) {
+  std::vector<std::thread> pool;
+  pool.reserve(n);
+  int th = 0;
+  try {
+    for (; th < n - 1; ++th) pool.emplace_back(std::cref(f), th);
+  } catch (const std::exception&) {   // (std::system_error, or no memory for the thread)
+  }
+  for (; th < n; ++th) f(th);
+  for (auto& t : pool) t.join();
 }
 
 // ---------------------------------------------------------------------------
@@ -596,12 +614,10 @@ dg_status dg_set_mesh(dg_ctx* c, int nElems, int Ngeo, const double* X, int nSid
     const int nth = host_threads(nElems, 64);
     std::vector<int> bad_elem(nth, -1);
     std::vector<double> bad_J(nth, 0.0);
-    std::vector<std::thread> pool;
-    for (int th = 0; th < nth; ++th) {
+    on_threads(nth, [&](int th) {
       const int e0 = (int)((long long)nElems * th / nth), e1 = (int)((long long)nElems * (th + 1) / nth);
-      pool.emplace_back(elem_block, e0, e1, &bad_elem[th], &bad_J[th]);
-    }
-    for (auto& th : pool) th.join();
+      elem_block(e0, e1, &bad_elem[th], &bad_J[th]);
+    });
     for (int th = 0; th < nth; ++th)
       if (bad_elem[th] >= 0) {
         char buf[128];
@@ -646,13 +662,12 @@ dg_status dg_set_mesh(dg_ctx* c, int nElems, int Ngeo, const double* X, int nSid
   };
   {
     const int nth = host_threads(nElems, 64);
-    std::vector<std::thread> pool;
-    for (int th = 0; th < nth; ++th) {
+    on_threads(nth, [&](int th) {
       const int s0 = (int)((long long)nSides * th / nth), s1 = (int)((long long)nSides * (th + 1) / nth);
       const int e0 = (int)((long long)nElems * th / nth), e1 = (int)((long long)nElems * (th + 1) / nth);
-      pool.emplace_back([&, s0, s1, e0, e1]() { side_block(s0, s1); wj_block(e0, e1); });
-    }
-    for (auto& th : pool) th.join();
+      side_block(s0, s1);
+      wj_block(e0, e1);
+    });
   }
   // |Omega|, summed element by element in index order (independent of the thread count)
   double vol = 0.0;
@@ -690,9 +705,7 @@ static dg_status upload_face(dg_ctx* c, const std::vector<double>& nvec) {
     }
   };
   const int nth = host_threads(c->nSides, 256);
-  std::vector<std::thread> pool;
-  for (int th = 0; th < nth; ++th) pool.emplace_back(side_block, nS * th / nth, nS * (th + 1) / nth);
-  for (auto& th : pool) th.join();
+  on_threads(nth, [&](int th) { side_block(nS * th / nth, nS * (th + 1) / nth); });
   if (zero) return fail(c, DG_ERR_MESH, "zero face normal");
   c->n_const_side = (int)std::count(same.begin(), same.end(), 1);
   std::vector<int> efc(c->efc);

@@ -193,3 +193,40 @@ def test_affine_metrics_snapped_constant(dgx, orc, N, nodes, rot):
         dgx.dg_destroy(ctx)
     Jc = Jc.reshape(9, curved.nElems, -1)
     assert not (Jc == Jc[:, :, :1]).all(axis=(0, 2)).any()
+
+
+def test_mesh_setup_without_threads():
+    """Where the process gets no more threads (here: a default stack that does
+    not fit its address space), the set-up runs on the calling one."""
+    import resource
+    import subprocess
+    import sys
+    code = """
+import threading
+import numpy as np
+from paper_2605_28627_amd import dgx, inputs as I
+try:
+    threading.Thread(target=print).start()
+    raise SystemExit("the limit does not hold")
+except RuntimeError:
+    pass
+ctx = dgx.dg_create(dgx.make_config(2))
+dgx.dg_set_mesh(ctx, I.box_mesh((8, 8, 8), (0.0,) * 3, (1.0,) * 3))
+sJ = dgx.dg_get_metrics(ctx)[2]
+assert np.allclose(sJ, 16.0 ** 3, rtol=1e-12)
+dgx.dg_destroy(ctx)
+print("done")
+"""
+
+    hard = resource.getrlimit(resource.RLIMIT_STACK)[1]
+    if hard != resource.RLIM_INFINITY and hard < 64 << 30:
+        pytest.skip("the stack limit cannot be raised")
+
+    def limits():
+        resource.setrlimit(resource.RLIMIT_AS, (32 << 30, 32 << 30))
+        resource.setrlimit(resource.RLIMIT_STACK, (64 << 30, hard))
+
+    env = dict(os.environ, OPENBLAS_NUM_THREADS="1", OMP_NUM_THREADS="1", PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120, env=env, cwd=ROOT,
+                       preexec_fn=limits)
+    assert r.returncode == 0 and "done" in r.stdout, (r.returncode, r.stdout[-500:], r.stderr[-1500:])
