@@ -831,6 +831,9 @@ dg_status dg_upload_metrics(dg_ctx* c, const double* Ja, const double* sJ, const
   const size_t nv = (size_t)c->nElems * c->n3, nf = (size_t)c->nSides * c->n2;
   for (size_t t = 0; t < nv; ++t)
     if (!(sJ[t] > 0.0) || !std::isfinite(sJ[t])) return fail(c, DG_ERR_MESH, "dg_upload_metrics: sJ must be positive");
+  for (size_t t = 0; t < nf; ++t)   // (upload_face's condition, before anything is replaced)
+    if (!(nvec[t] * nvec[t] + nvec[nf + t] * nvec[nf + t] + nvec[2 * nf + t] * nvec[2 * nf + t] > 0.0))
+      return fail(c, DG_ERR_MESH, "dg_upload_metrics: zero face normal");
   HIPCHK(c, hipMemcpy(c->d_Ja, Ja, 9 * nv * sizeof(double), hipMemcpyHostToDevice));
   HIPCHK(c, hipMemcpy(c->d_sJ, sJ, nv * sizeof(double), hipMemcpyHostToDevice));
   std::vector<double> nv3(nvec, nvec + 3 * nf);

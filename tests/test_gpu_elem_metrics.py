@@ -121,3 +121,29 @@ def test_uploaded_metrics_are_examined_again(S):
     finally:
         s.close()
     assert np.array_equal(R0, R1)
+
+
+def test_rejected_metrics_change_nothing(S):
+    """A face normal of zero length is refused before anything is replaced: the
+    context goes on with its old terms, and the per-element copies can still be
+    switched off and on."""
+    from paper_2605_28627_amd import dgx
+    mesh = I.box_mesh((2, 3, 2), (-PI,) * 3, (PI,) * 3, rotate_seed=3)
+    s = S(dict(N=3, nodes=1, form=1, physics=1, mu=1e-2), mesh, "cuda:0")
+    try:
+        _, Ja, sJ, nv = s.metrics()
+        U = s.init_state(I.smooth_random_state(s.coords(), 6, amp=0.2))
+        R = [s.rhs(U).cpu().numpy()]
+        bad = nv.copy()
+        bad[:, 5] = 0.0
+        with pytest.raises(dgx.DGError) as ei:
+            s.upload_metrics(2.0 * Ja, 0.5 * sJ, bad)
+        assert ei.value.status == dgx.DG_ERR_MESH
+        assert all(np.array_equal(a, b) for a, b in zip(s.metrics()[1:], (Ja, sJ, nv)))
+        R.append(s.rhs(U).cpu().numpy())
+        s.set_element_metrics(False)
+        s.set_element_metrics(True)
+        R.append(s.rhs(U).cpu().numpy())
+    finally:
+        s.close()
+    assert np.array_equal(R[0], R[1]) and np.array_equal(R[0], R[2])
