@@ -226,7 +226,8 @@ dg_status dg_lift(dg_ctx* ctx, const double* U, double* g, void* stream);
 /* nsteps steps of the context's low-storage RK scheme (LSERK4(5) or
  * LSERK4-14) with fixed dt, in place: per stage s
  * dU <- A_s dU + dt R(U); U <- U + B_s dU.  dU is the 2N-storage register
- * (device, state length); it is zeroed by the call before the first stage. */
+ * (device, state length): its contents on entry are ignored, whatever they
+ * are (A_1 = 0: the first stage overwrites dU and does not read it). */
 dg_status dg_rk_step(dg_ctx* ctx, double* U, double* dU, double t, double dt, int nsteps, void* stream);
 
 /* One step of dg_rk_step (same arithmetic) that also keeps its stage inputs

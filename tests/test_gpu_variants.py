@@ -195,3 +195,40 @@ def test_affine_adjoint(S, orc, N, nodes, physics):
     for a, b in zip(on, off):
         assert np.isfinite(a).all()
         assert np.abs(a - b).max() <= 1e-12 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("case", [(3, 0, 0, 0, 0, 0), (7, 1, 0, 1, 0, 0), (3, 0, 1, 1, 0, 0), (5, 1, 1, 0, 0, 0),
+                                  (7, 1, 1, 1, 0, 0), (7, 1, 1, 1, 1, 0), (1, 0, 0, 0, 0, 1), (3, 1, 1, 1, 0, 1),
+                                  (5, 0, 0, 0, 0, 1)], ids=str)
+def test_register_contents_on_entry_are_ignored(S, case):
+    """rk_step, rk_step_stages and the reverse step (its own register too) with
+    a register of NaN give bitwise what they give with one of zeros."""
+    import torch
+    _say("register", case)
+    N, nodes, form, physics, integrator, fv = case
+    mesh = I.box_mesh((3, 2, 2), (-PI,) * 3, (PI,) * 3, rotate_seed=8)
+    cfg = dict(N=N, nodes=nodes, form=form, physics=physics, mu=0.02 if physics else 0.0, integrator=integrator, fv=fv)
+    s = S(cfg, mesh, adjoint=not fv)
+    try:
+        U0 = s.init_state(I.smooth_random_state(s.coords(), 77, amp=0.1))
+        if fv:
+            s.fv_switch(U0, (np.arange(mesh.nElems) % 2).astype(np.int32))
+        dt = 0.2 * s.timestep(U0, 0.9)
+        lam0 = s.to_device(np.random.default_rng(78).normal(size=s.state_shape))
+        out = []
+        for fill in (0.0, float("nan")):
+            s.ws[: s.ws.numel() // 8 * 8].view(torch.float64).fill_(fill)   # (scratch: all of it is written before it is read)
+            U, dU = U0.clone(), torch.full_like(U0, fill)
+            s.rk_step(U, dU, dt, 2)
+            res = [U, dU]
+            if not fv:
+                V, dV, Y = U0.clone(), torch.full_like(U0, fill), s.stage_buffer()
+                s.rk_step_stages(V, dV, dt, Y)
+                lam, lamd = lam0.clone(), torch.full_like(U0, fill)
+                s.adjoint_rk_step(U0, lam, lamd, dt)
+                res += [V, dV, Y, lam]
+            out.append(res)
+        for a, b in zip(*out):
+            assert torch.isfinite(a).all() and torch.equal(a, b)
+    finally:
+        s.close()
