@@ -232,3 +232,71 @@ def test_register_contents_on_entry_are_ignored(S, case):
             assert torch.isfinite(a).all() and torch.equal(a, b)
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("physics", [0, 1])
+@pytest.mark.parametrize("curved,twopoint", [(0.0, 0), (0.1, 0), (0.1, 1)])
+@pytest.mark.parametrize("N", [4, 5, 6])
+def test_pair_exchange(S, orc, N, curved, twopoint, physics):
+    """Lobatto split form on lines that straddle wavefronts: the residual hands
+    each pair's second share over through LDS at every distance (N + 1 odd: none
+    is met from both ends, N = 5: one is), the adjoint too for Chandrashekar's
+    flux.  Element counts that leave work-items idle, random side orientations;
+    oracle bounds as for all residuals, steps and transposed residuals."""
+    _say("exchange", N, curved, twopoint, physics)
+    mesh = I.box_mesh((2, 3, 2), (-PI,) * 3, (PI,) * 3, Ngeo=N if curved else 1, curved_amp=curved, rotate_seed=10)
+    cfg = dict(N=N, nodes=1, form=1, physics=physics, mu=0.02 if physics else 0.0, twopoint=twopoint)
+    o, s = orc.Oracle(cfg, mesh), S(cfg, mesh, adjoint=True)
+    try:
+        _, J, Ja = o.geometry()
+        s.upload_metrics(Ja, 1.0 / J, o.face_normals())
+        # (variations on both sides of the log means' series threshold)
+        U = I.smooth_random_state(o.coords(), 91, amp=0.2)
+        U[:, ::2] = I.smooth_random_state(o.coords(), 91, amp=0.002)[:, ::2]
+        Ug = s.init_state(U)
+        err = rel_err_per_var(s.rhs(Ug).cpu().numpy(), o.rhs(U))
+        lam = np.random.default_rng(92).normal(size=U.shape)
+        adj = _off(s.adjoint_rhs(Ug, s.to_device(lam)).cpu().numpy(), o.rhs_vjp(U, lam))
+        dt = 0.5 * o.timestep(U, 0.9)
+        s.rk_step(Ug, s.empty_state(), dt, 1)
+        step = _off(Ug.cpu().numpy() - U, o.lserk(U, 1, dt) - U)
+    finally:
+        s.close()
+    _say("exchange", N, curved, twopoint, physics, err.max(), adj, step)
+    assert np.all(err < 1e-12) and adj < 1e-12 and step < 1e-11
+
+
+@pytest.mark.parametrize("K", [(1, 1, 1), (3, 1, 1), (3, 3, 1)], ids=str)
+@pytest.mark.parametrize("nodes,form", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("physics", [0, 1])
+def test_packed_elements_steps(S, orc, K, nodes, form, physics):
+    """N = 1, the kernels that test_packed_elements leaves out: the reverse step,
+    and of FV contexts the step, the indicator and the switch with a register."""
+    _say("packed steps", K, nodes, form, physics)
+    mesh = I.box_mesh(K, (-PI,) * 3, (PI,) * 3, rotate_seed=4)
+    cfg = dict(N=1, nodes=nodes, form=form, physics=physics, mu=0.02 if physics else 0.0)
+    o, s = orc.Oracle(cfg, mesh), S(cfg, mesh, adjoint=True)
+    of, f = orc.Oracle(dict(cfg, fv=1), mesh), S(dict(cfg, fv=1), mesh)
+    try:
+        _, J, Ja = o.geometry()
+        for x in (s, f):
+            x.upload_metrics(Ja, 1.0 / J, o.face_normals())
+        U = I.smooth_random_state(o.coords(), 93, amp=0.1)
+        rng = np.random.default_rng(94)
+        lam, reg = rng.normal(size=U.shape), rng.normal(size=U.shape)
+        dt = o.timestep(U, 0.9)
+        lamU = s.to_device(lam)
+        s.adjoint_rk_step(s.to_device(U), lamU, s.empty_state(), dt)
+        assert _off(lamU.cpu().numpy(), o.lserk_adjoint(U, lam, 1, dt)) < 1e-12
+        mask = (np.arange(mesh.nElems) % 3 == 0).astype(np.int32)
+        Uf, dUf = f.init_state(U), f.to_device(reg)
+        ind, ref = f.fv_indicator(Uf).cpu().numpy(), of.indicator(U)
+        assert np.abs(ind - ref)[ref > -12].max(initial=0.0) < 1e-9
+        f.fv_switch(Uf, mask, dU=dUf)
+        Uo, dUo = of.fv_switch(U, reg, mask)
+        assert _off(Uf.cpu().numpy(), Uo) < 1e-13 and _off(dUf.cpu().numpy(), dUo) < 1e-12
+        f.rk_step(Uf, dUf, dt, 2)
+        assert _off(Uf.cpu().numpy() - Uo, of.lserk(Uo, 2, dt) - Uo) < 1e-11
+    finally:
+        s.close()
+        f.close()
