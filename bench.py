@@ -267,7 +267,7 @@ def lift_kernel_bytes_per_dof(w, precision=0, elem_frac=0.0, merged=False):
     return 8.0 * (reads + writes)
 
 
-def adjoint_kernel_bytes_per_dof(w, elem_frac=0.0):
+def adjoint_kernel_bytes_per_dof(w, elem_frac=0.0, merged=False):
     """Compulsory HBM bytes per node of one launch of each kernel of an
     adjoint stage (dg_adjoint_rk_step; the stage's reverse RK update fused
     into its last kernel), 8 bytes per value, per face node values times
@@ -286,24 +286,35 @@ def adjoint_kernel_bytes_per_dof(w, elem_frac=0.0):
       k_adj_lift_volume (Navier-Stokes): 1/J 1, the own trace 5 fpn, both
         Qbar 8 fpn, out 5, lamU 5, lamdU 5; writes lamU and lamdU 10 and the
         next stage's surface adjoint 5 fpn.
-    Ja and 1/J as in the residual kernel (metric_values_per_dof).
-    The kernels read less than this table: k_adj_volume takes the own side's
-    gradient alone (on LGL nodes, with the own trace, from the node arrays,
-    and k_lift writes no gradient traces there), k_trace and k_adj_trace are
-    one launch where both are needed, and plane faces have their geometry
-    once per side."""
+    Ja and 1/J as in the residual kernel (metric_values_per_dof).  This is the
+    stage with every part a launch of its own and both sides' face values read.
+
+    merged: as the kernels run it.  k_adj_begin takes the place of k_trace and
+    the surface adjoint where both are needed (Euler: every stage; else a
+    step's first): U 5, lambda 5 (written back, scaled, in a step's first
+    stage: not counted), 1/J 1; writes 10 fpn.  k_adj_volume reads the own
+    side's gradient alone, on LGL nodes, with the own trace, from the node
+    arrays, so that k_lift writes no gradient traces there; for the fraction
+    elem_frac of elements the face geometry is read once per side."""
     n1 = w["N"] + 1
     fpn = 6 * n1 * n1 / n1 ** 3
-    ns = w["physics"] == 1
+    ns, lgl = w["physics"] == 1, w["nodes"] == 1
     m10, m1 = metric_values_per_dof(w, elem_frac), metric_values_per_dof(w, elem_frac, 1)
-    b = {"k_trace": 5 + 5 * fpn,
-         "k_adj_trace": 5 + m1 + 5 * fpn}
-    vol_r = 5 + 5 + m10 + 24 * fpn + (12 + 24 * fpn if ns else 5)
-    vol_w = 5 + 4 * fpn if ns else 10
-    b["k_adj_volume"] = vol_r + vol_w
+    traces = 5 if lgl else 10
+    b = {"k_trace": 5 + 5 * fpn}
+    if merged:
+        face = 4 * (1.0 - elem_frac * (1 - 1 / n1 ** 2))
+        b["k_adj_begin"] = 10 + m1 + 10 * fpn
+        vol_r = 5 + 5 + m10 + (traces + 10 + face) * fpn + (12 * (1.0 if lgl else 1.0 + fpn) if ns else 5)
+        grad_w = 12 if lgl else 12 + 12 * fpn
+    else:
+        face = 4
+        b["k_adj_trace"] = 5 + m1 + 5 * fpn
+        vol_r = 5 + 5 + m10 + 24 * fpn + (12 + 24 * fpn if ns else 5)
+        grad_w = 12 + 12 * fpn
+    b["k_adj_volume"] = vol_r + (5 + 4 * fpn if ns else 10)
     if ns:
-        traces = 5 if w["nodes"] == 1 else 10
-        b["k_lift_gradients"] = 5 + m10 + (traces + 4) * fpn + 12 + 12 * fpn
+        b["k_lift_gradients"] = 5 + m10 + (traces + face) * fpn + grad_w
         b["k_adj_lift_volume"] = m1 + 15 + 13 * fpn + 10 + 5 * fpn
     return {k: 8.0 * v for k, v in b.items()}
 

@@ -174,18 +174,20 @@ __global__ __launch_bounds__(Shape<N>::block) void k_adj_begin(Geo G, Phys P, co
 // summed along the line.  Phase 4 maps them back through the projection:
 // (du/dv)^T at each face node, l_f along the lines, (dv/dU)^T at each node.
 // Waves per SIMD requested for 512-work-item adjoint kernels.  The affine
-// variant on LGL nodes fits two elements per CU: 74 KB of LDS (no staged
-// w_r, no metric rows) and 128 VGPRs with 28 B of spills (Euler: none); one
+// variant on LGL nodes fits two elements per CU: 79 KB of LDS (no staged
+// w_r, no metric rows) and 128 VGPRs with 28 B of scratch (Euler: 12); one
 // element per CU left the SIMDs two waves each, 43 % busy (16^3 reverse step
-// 4.61 -> 3.95 ms, Euler 12^3 1.21 -> 0.93 ms).  The others hold 170-256
-// registers: at 128 they spill hundreds of bytes, so they keep one.
+// 4.61 -> 3.95 ms, Euler 12^3 1.21 -> 0.93 ms).  The others hold 163-256
+// registers: at 128 they spill hundreds of bytes, so they keep one (the weak
+// form's Euler kernel has no such bound to meet: 102 on Gauss nodes, 134 on
+// Lobatto nodes).
 template <int N, int NODES, int VAR>
 constexpr int adj_waves() {
   return Shape<N>::nth >= 512 ? (VAR == 1 && NODES == 1 ? 4 : 1) : 1;
 }
 //
 // VAR 1 (split form, every element affine, Chandrashekar's flux): uniform
-// metric terms in scalar registers, no metric rows in LDS, the central flux
+// metric terms in registers, no metric rows in LDS, the central flux
 // compiled out (as k_volume).  VAR 2: the central flux compiled out, metric
 // terms from the node arrays.
 template <int N, int NODES, int FORM, int PHYS, int ROE = 0, int VL = 0, int VAR = 0>

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(Shape<N>::block) void k_trace_fv(Geo G, Phys P, con
 #pragma unroll
       for (int v = 0; v < 5; ++v) snod[v * n3 + t] = w[v];
     }
-    __syncthreads();   // (efl is uniform: every work-item gets here)
+    __syncthreads();   // (efl is the element's: all of its work-items get here)
   }
   for (int ft = t; ft < S::nface; ft += S::nth) {
     const int f = ft / n2, rr = ft % n2, pp = rr % n1, qq = rr / n1, r = f / 2;
@@ -426,6 +426,8 @@ __global__ __launch_bounds__(Shape<N>::block) void k_lift_fv(Geo G, Phys P, cons
 // ---------------------------------------------------------------------------
 // Three waves per SIMD at N = 3, Navier-Stokes (165 VGPRs, no spills; left to
 // itself the compiler takes 183 and two waves: 32^3 half FV 4.47 -> 4.34 ms).
+// At N = 1 (187 VGPRs) that bound loses 2-3 % (42^3, all FV: 4.73 -> 4.85 ms);
+// N = 2 (179) has two waves as well and was left there.
 template <int N, int MODE, int PHYS = 0>
 __global__ __launch_bounds__(Shape<N>::block, PHYS == 1 && N == 3 ? 3 : 1) void k_fv(Geo G, Phys P, const double* __restrict__ U,
                                                       const double* __restrict__ Utr, const double* __restrict__ gin,

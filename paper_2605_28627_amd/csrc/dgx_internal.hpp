@@ -13,7 +13,6 @@ namespace dgx {
 constexpr int kMaxN = 7;
 constexpr int kMaxN1 = kMaxN + 1;
 
-// Device copy of the 1-D operators of one context (all FP64).
 // Lobatto nodes in double: the lifting adds its own side's half of the viscous
 // surface flux to the viscous volume term at the face nodes, where the residual
 // kernel used to subtract it again from both sides' fluxes; that kernel then
@@ -21,6 +20,7 @@ constexpr int kMaxN1 = kMaxN + 1;
 // mode keeps both in the surface flux, rounded as it stores them.
 constexpr bool own_visc_in_volume(int nodes, int prec) { return nodes == 1 && prec == 0; }
 
+// Device copy of the 1-D operators of one context (all FP64).
 struct DevBasis {
   double w[kMaxN1];               // quadrature weights
   double winv[kMaxN1];            // 1 / w
@@ -123,10 +123,11 @@ struct Cfg {
 // result of hipGetLastError() after the launch.
 // Face traces of U (entropy-projected for the split form on Gauss nodes).
 hipError_t launch_trace(const Cfg& c, const Geo& g, const Phys& p, const double* U, double* Utr, hipStream_t s);
-// BR1 lifting.  emit 0: gradients g [12][nE][n3] and their traces
-// [2][12][nSides][n2].  emit 1: the viscous fluxes the residual needs,
-// G~^r [4r+v][nE][n3] and the per-side face-normal fluxes [2][4][nSides][n2]
-// (in the buffers of g and of the traces).
+// BR1 lifting.  emit 0: gradients g [12][nE][n3] and, on Gauss nodes, their
+// traces [2][12][nSides][n2] (on Lobatto nodes they are the face nodes' own
+// gradients).  emit 1: what the residual needs, the viscous volume term
+// [4][nE][n3] (own_visc_in_volume: with the own half of the surface flux) and
+// the per-side face-normal fluxes [2][4][nSides][n2], in the same buffers.
 hipError_t launch_lift(const Cfg& c, int emit, const Geo& g, const Phys& p, const double* U, const double* Utr,
                        double* gout, double* gtr, hipStream_t s);
 // mode 0: Ut = R(U).  mode 1: dU = A dU + dt R(U); U += B dU; traces of the new U -> Utr_next.
@@ -148,12 +149,11 @@ struct AdjUpd {
 };
 
 // out = (dR/dU)^T lam (or, with up.lamU, the fused update); Utr holds the
-// traces of U, Lbar/qbar are scratch (Navier-Stokes: gin/gtr hold the
-// forward lifted gradients and their traces, qbar [2][4][nSides][n2] takes
-// the lifting adjoint's face values, and out is scratch too when the update
-// is fused).
-// (Lbar, the surface adjoint of lam, written by launch_adj_begin or by the
-// previous stage's last kernel.)
+// traces of U and Lbar the surface adjoint of lam (written by launch_adj_begin
+// or by the previous stage's last kernel).  Navier-Stokes: gin holds the
+// forward lifted gradients, gtr their traces (Gauss nodes only), qbar
+// [2][4][nSides][n2] takes the lifting adjoint's face values, and out is
+// scratch too when the update is fused.
 hipError_t launch_adjoint(const Cfg& c, const Geo& g, const Phys& p, const double* U, const double* lam,
                           const double* Utr, double* Lbar, const double* gin, const double* gtr, double* out,
                           double* qbar, const AdjUpd& up, hipStream_t s);

@@ -143,6 +143,7 @@ __device__ inline double ld_visc(const double* p, size_t i) {
 // meshes an N = 7 LGL element's 50 KB of LDS let three of them share a CU, and
 // its registers fit in 80 without spills (32^3, 2 steps: 21.7 -> 21.2 ms;
 // with 92 registers and two elements per CU the LDS would stay half empty).
+// N = 4, 5, 6 take 73 to 80 registers by themselves.
 template <int N, int NODES, int EMIT, int AFF>
 constexpr int lift_waves() {
   return AFF && N == 7 && NODES == 1 && EMIT == 1 ? 6 : 1;
@@ -170,11 +171,12 @@ constexpr int lift_waves() {
 // reconstructed face states (h^2 (B^-1 x B^-1), h = 2/(N+1)), and instead of
 // the face-normal viscous flux the element writes the layer-0 sub-cell means
 // of its gradient, B3(J g)/V, to gtr + 8 nSides n2 ([slot][12][side][fi]).
-// ---------------------------------------------------------------------------
 //
 // AFF 1 (every element affine, every side with one normal): the metric terms
-// are uniform over the workgroup and live in scalar registers, and the face
-// averages share the LDS of the viscous fluxes, which are formed after them.
+// are uniform over the element and live in registers (scalar ones, unless
+// elements share a wavefront: N = 1), and the face averages share the LDS of the
+// viscous fluxes, which are formed after them.
+// ---------------------------------------------------------------------------
 template <int N, int NODES, int EMIT, int PREC, int VL, int FV = 0, int AFF = 0>
 __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>())) void k_lift(Geo G, Phys P, const double* __restrict__ U,
                                                         const double* __restrict__ Utr, double* __restrict__ gout,
@@ -694,7 +696,7 @@ __global__ __launch_bounds__(Shape<N>::block, (lift_waves<N, NODES, EMIT, AFF>()
 // element's LDS small enough for three waves per SIMD at N=3.
 __host__ __device__ constexpr int es_face_slot(int f) { return f < 4 ? f : f - 4; }
 constexpr int kEsFaceSlots = 4;
-template <int N, int NODES, int FORM, int VAR = 0>
+template <int N, int NODES, int FORM>
 constexpr int volume_waves() {
   return Shape<N>::nth >= 512 ? 4 : ((FORM == 1 && NODES == 0 && N == 3) ? DGX_ES_WAVES : 1);
 }
@@ -709,19 +711,22 @@ constexpr int volume_waves() {
 // gvf + 8 nSides n2.
 //
 // VAR 1 (split form, every element of the mesh affine, Chandrashekar's flux):
-// the metric terms are uniform over the workgroup and live in scalar
-// registers; no metric rows in LDS (N = 7: 12 KB), none read per pair, and on
+// the metric terms are uniform over the element and live in registers (as in
+// k_lift); no metric rows in LDS (N = 7: 12 KB), none read per pair, and on
 // Lobatto nodes no barriers between directions whose pairs stay inside a
-// wavefront (sweep_begin_barrier).  The
-// central two-point flux is compiled out of the pair loops, where it cost 10-20
-// registers as a run-time choice.  N = 7 Navier-Stokes: 105 VGPRs and 66 KB
-// instead of 122 and 78; 32^3 (2 steps) 23.2 -> 22.5 ms, 16^3 (4 steps)
-// 5.87 -> 5.57 ms, N = 5 Euler 20^3 3.76 -> 3.25 ms.
+// wavefront (sweep_begin_barrier).  The central two-point flux is compiled out
+// of the pair loops, where it cost 10-20 registers as a run-time choice (N = 7
+// Navier-Stokes: 106 VGPRs and 66 KB instead of 122 and 78).
+// Against VAR 0 on the same meshes: N = 7 Navier-Stokes 32^3 (2 steps) 21.7 ->
+// 20.8 ms, 16^3 (4 steps) 5.53 -> 5.27 ms, on Gauss nodes 15x14x16 (2 steps) 5.32
+// -> 4.93 ms; N = 5 Euler 20^3 (4 steps) 3.23 -> 2.75 ms; N = 3 Gauss 48^3 7.13 ->
+// 6.95 ms.
 // VAR 2: the central flux compiled out, metric terms from the node arrays (any
 // mesh; curved N = 5: 111 instead of 138 VGPRs, four waves per SIMD instead of
-// three, 24^3 (2 steps) 5.50 -> 5.23 ms).  VAR 0: either two-point flux, Roe.
+// three, 24^3 (2 steps) 5.34 -> 5.05 ms).  VAR 0: either two-point
+// flux, Roe.
 template <int N, int NODES, int FORM, int PHYS, int PREC, int MODE, int ROE, int FV = 0, int VAR = 0>
-__global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM, VAR>())) void k_volume(Geo G, Phys P, const double* __restrict__ U,
+__global__ __launch_bounds__(Shape<N>::block, (volume_waves<N, NODES, FORM>())) void k_volume(Geo G, Phys P, const double* __restrict__ U,
                                                           const double* __restrict__ Utr,
                                                           const double* __restrict__ gvn,
                                                           const double* __restrict__ gvf, double* __restrict__ Ut,

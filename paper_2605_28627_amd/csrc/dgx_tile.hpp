@@ -20,6 +20,10 @@ struct Shape {
   // 4.55 -> 2.47 ms; 8 elements of 8 gain nothing more there and lose 5 % on
   // meshes that do not fill the chip, 2 of 32 lose 17 % at 60^3).  N = 2 packed
   // in pairs (27 of 32) gained 6 % at 40^3 and lost 9 % at 5x6x5.
+  // What is uniform over the workgroup elsewhere (metric terms, element and
+  // face flags) then differs between a wavefront's elements.  Returns and
+  // barriers that depend on it are safe: the workgroup is that one wavefront,
+  // whose LDS accesses stay in order and whose barriers wait for nobody.
   static constexpr int nth = N == 1 ? 16 : ((n3 + 63) / 64) * 64;
   static constexpr int epb = nth < 64 ? 64 / nth : 1;  // elements per workgroup
   static constexpr int block = nth * epb;
@@ -55,7 +59,7 @@ struct VolBasis {
 // The basis copy in two parts, so that its loads are in flight together with
 // the element's own and nothing waits for them alone: load() at the start of a
 // kernel, store() to LDS before the first barrier.  At most one value per
-// work-item (FVB, N = 3: two); loaded array by array and stored at once it cost
+// work-item (FVB, N = 1 and 3: two); loaded array by array and stored at once it cost
 // every workgroup two memory latencies before its first load of the state.
 template <int N, bool FVB, int NTH>
 struct BasisCopy {
@@ -79,7 +83,7 @@ struct BasisCopy {
 // same at all of its nodes (affine), the per-element copy G.em, whose 1/J is
 // positive exactly for those elements.  Such an element's nodes all read the
 // copy and the node arrays are not touched (same values).
-// Selects only, no branches; base and st are uniform over the workgroup.
+// Selects only, no branches; base and st are uniform over the element.
 struct NodeMetric {
   const double* base;
   size_t off, st;

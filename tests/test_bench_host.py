@@ -75,3 +75,33 @@ def test_cpu_baseline_leg_runs_on_the_host():
     out = bench.cpu_baseline(args, cfg, mesh, U, 1e-9)
     assert out["kind"] == "oracle" and out["cores"] == 1 and out["value"] > 0
     assert out["host"]["nproc"] >= 1 and "O3" in out["build"]
+
+
+def test_merged_byte_models():
+    """What the kernels of plain runs leave out of the tables above, value by value (N = 7: 0.75 face nodes per node)."""
+    c2, es = I.WORKLOADS["ns_split_lgl_n7_16x16x16_tgv"], I.WORKLOADS["ns_split_lg_n3_64x64x64_freestream"]
+    # curved LGL: the other side's trace 5 and viscous flux 4, face geometry 4 per face node
+    assert bench.volume_kernel_bytes_per_dof(c2, merged=True) == 8 * (5 + 10 + 4 + 4 + 0.75 * (5 + 4 + 4) + 5 + 5 + 0.75 * 5)
+    # float fluxes: both sides' viscous fluxes, 4 bytes each
+    assert bench.volume_kernel_bytes_per_dof(c2, precision=1, merged=True) == \
+        8 * (5 + 10 + 4 + 4 + 0.75 * (5 + 4 + 4) + 5 + 5 + 0.75 * 5)
+    # affine: metric terms once per element, face geometry once per side (64 face nodes)
+    assert bench.volume_kernel_bytes_per_dof(c2, elem_frac=1.0, merged=True) == \
+        pytest.approx(8 * (5 + 10 / 512 + 4 + 4 + 0.75 * (5 + 4 + 4 / 64) + 5 + 5 + 0.75 * 5))
+    assert bench.lift_kernel_bytes_per_dof(c2, elem_frac=1.0, merged=True) == \
+        pytest.approx(8 * (5 + 10 / 512 + 0.75 * (5 + 4 / 64) + 4 + 0.75 * 4))
+    # Gauss nodes: both sides' traces and viscous fluxes (1.5 face nodes per node at N = 3)
+    assert bench.volume_kernel_bytes_per_dof(es, elem_frac=1.0, merged=True) == \
+        pytest.approx(8 * (5 + 10 / 64 + 4 + 4 + 1.5 * (10 + 8 + 4 / 16) + 5 + 5 + 1.5 * 5))
+    a = bench.adjoint_kernel_bytes_per_dof(c2, elem_frac=1.0, merged=True)
+    assert "k_adj_trace" not in a
+    assert a["k_adj_begin"] == pytest.approx(8 * (5 + 5 + 1 / 512 + 0.75 * 10))
+    # lambda, U, metric, g 12, per face node the other trace 5, both surface adjoints 10; out 5, Qbar 4 per face node
+    assert a["k_adj_volume"] == pytest.approx(8 * (5 + 5 + 10 / 512 + 12 + 0.75 * (5 + 10 + 4 / 64) + 5 + 0.75 * 4))
+    assert a["k_lift_gradients"] == pytest.approx(8 * (5 + 10 / 512 + 0.75 * (5 + 4 / 64) + 12))
+    g = bench.adjoint_kernel_bytes_per_dof(es, merged=True)
+    assert g["k_adj_volume"] == pytest.approx(8 * (5 + 5 + 10 + 12 + 1.5 * (10 + 10 + 4 + 12) + 5 + 1.5 * 4))
+    assert g["k_lift_gradients"] == pytest.approx(8 * (5 + 10 + 1.5 * (10 + 4) + 12 + 1.5 * 12))
+    e = bench.adjoint_kernel_bytes_per_dof(I.WORKLOADS["euler_split_lgl_n5_8x8x8_tgv"], elem_frac=1.0, merged=True)
+    assert set(e) == {"k_trace", "k_adj_begin", "k_adj_volume"}
+    assert e["k_adj_volume"] == pytest.approx(8 * (5 + 5 + 10 / 216 + (5 + 10 + 4 / 36) + 5 + 10))
